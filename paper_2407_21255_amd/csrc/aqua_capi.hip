@@ -33,12 +33,6 @@ constexpr uint32_t kHostZeroCopyWorkgroups = 16;
 
 // Measurement switches: the defaults are the shipped configuration, the
 // macros exist so that sweeps can build variants.
-// Smallest workgroup of the swap kernels.  1024 lanes for every chunk size:
-// workgroups sized to 32 KiB chunks (512 lanes) measured no faster, and to
-// 16 KiB chunks (256 lanes) 4 % slower.
-#ifndef AQUA_MIN_THREADS
-#define AQUA_MIN_THREADS 1024
-#endif
 // 1: HBM-target calls read their descriptors from the device ring too.
 // Off: reading them in place from the pinned ring measured as fast or faster
 // (no upload kernel on the stream).
@@ -611,7 +605,8 @@ aqua::SwapLaunch make_launch(aqua_kv_pool* p, bool is_in, uint8_t* img, const Ru
     L.pool_lstride = (uint64_t)p->shape.N * p->shape.C;
     L.max_workgroups = p->max_wg[target];
     L.nt_pool_store = aqua::nt_pool_store(p->shape.C, (uint64_t)nl * p->call_blocks * p->shape.C);
-    L.threads = aqua::swap_threads(p->shape.C, AQUA_MIN_THREADS);
+    L.threads = aqua::run_threads(p->call_blocks * p->shape.C / std::max<uint32_t>(1, ndesc),
+                                  L.max_workgroups != 0);
     L.xcd_order = false;
     return L;
 }

@@ -179,6 +179,11 @@ uint32_t swap_threads(uint64_t chunk_bytes, uint32_t min_threads) {
     return t;
 }
 
+uint32_t run_threads(uint64_t run_bytes, bool capped) {
+    if (capped || run_bytes >= kFullWorkgroupRun) return kMaxThreads;
+    return std::min<uint32_t>(kMaxThreads / 2, swap_threads(run_bytes * kUnroll, 64));
+}
+
 RunOrder run_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t num_blocks,
                    uint32_t num_seqs) {
     // Fewer blocks than two per XCD: nothing to deal out.

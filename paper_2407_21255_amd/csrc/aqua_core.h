@@ -94,13 +94,28 @@ static_assert(sizeof(RunDesc) == 32, "descriptor layout is shared with the kerne
 
 // Launch geometry of the copy kernels.  Every lane moves kUnroll 16-byte
 // vectors per pass, so a workgroup of `threads` lanes has threads * 64 bytes
-// in flight.  A workgroup is sized to the chunk: 1024 lanes for chunks of
-// 64 KiB and more, fewer for smaller chunks (down to min_threads, a power
-// of two of at least 64), so that every lane still issues kUnroll loads
-// before its first store.
+// in flight.  swap_threads sizes a workgroup so that every lane issues kUnroll
+// loads before its first store: 1024 lanes for 64 KiB and more, fewer for
+// less (down to min_threads, a power of two of at least 64).
 constexpr uint32_t kUnroll = 4;
 constexpr uint32_t kMaxThreads = 1024;
 uint32_t swap_threads(uint64_t chunk_bytes, uint32_t min_threads);
+
+// Lanes of a swap launch whose runs average `run_bytes`: 1024 from 16 KiB up,
+// below that one 16-byte vector per lane (a power of two of at least 64 and
+// at most 512 lanes).  What bounds short runs is the rate at which waves
+// start: a 1024-lane workgroup is 16 waves, and with 8 KiB runs half of them,
+// with 2 KiB runs 14 of 16, have nothing to copy.  Measured on MI355X, HBM
+// traffic of the gather at about 1.2 GiB per call, 1024 lanes against this
+// rule: 8 KiB runs 4.9 -> 6.1 TB/s, 4 KiB 3.0 -> 6.0, 2 KiB 1.6 -> 5.5;
+// scatters the same.  Two or four vectors per lane (fewer waves still) were
+// 1-7 % slower than one; 16 KiB runs took 1-5 % longer with 512 or 256 lanes
+// than with 1024, 10 to 12 KiB runs 4-6 % less with 512 than with 1024.
+// `capped` launches (a limited grid that loops over its units, such as the
+// zero-copy host path's 16 workgroups) keep 1024: there a workgroup's lanes
+// are what is in flight.
+constexpr uint64_t kFullWorkgroupRun = 16ull << 10;
+uint32_t run_threads(uint64_t run_bytes, bool capped);
 
 // Workgroups of one launch over `units` work units: one per unit, at most
 // `max_workgroups` when that is non-zero, and never more than kMaxGrid.  A

@@ -100,6 +100,10 @@ int64_t aqua_core_plan(const aqua_kv_desc* desc, uint32_t num_seqs,
     return (int64_t)plan.size();
 }
 
+uint32_t aqua_core_run_threads(uint64_t run_bytes, int32_t capped) {
+    return aqua::run_threads(run_bytes, capped != 0);
+}
+
 void* aqua_core_tracker_new(uint32_t num_blocks) {
     return new aqua::HazardTracker(num_blocks);
 }

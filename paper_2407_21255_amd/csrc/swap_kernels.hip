@@ -6,11 +6,9 @@
 // moves 16-byte vectors, a wave covers 1 KiB contiguous per instruction,
 // and kUnroll = 4 independent loads are issued before the first store, so a
 // workgroup of 1024 lanes (16 wave64s) holds one 64 KiB bf16 chunk in flight.
-// The kernels also come in 512, 256, 128 and 64 lanes, so that a launch can
-// size the workgroup to a smaller chunk and keep kUnroll loads in flight
-// per lane; on MI355X that measured no faster for 32 KiB chunks and 4 %
-// slower for 16 KiB ones than 1024 lanes with idle lanes in the last pass,
-// so the library launches 1024 lanes by default (swap_threads).
+// The kernels also come in 512, 256, 128 and 64 lanes: runs under 16 KiB are
+// bound by the rate at which waves start, so a launch takes no more waves
+// than its runs fill (run_threads).
 // The run descriptor is uniform across the workgroup and is fetched with
 // scalar loads.  The offload side is written (swap-out) or read (swap-in) with
 // nontemporal hints: it is touched once and should not displace the pool's
