@@ -160,6 +160,7 @@ struct aqua_kv_pool {
     std::vector<StagedSeq> sseq;
     std::vector<uint64_t> slot_offsets;  // per sequence, in a slot
     uint64_t call_blocks = 0;            // table entries of the call being enqueued
+    bool call_dealt = false;             // its runs are dealt out to the XCDs
 
     uint64_t next_ticket = 1;
     uint64_t unit_bytes = kDefaultUnitBytes;
@@ -604,7 +605,8 @@ aqua::SwapLaunch make_launch(aqua_kv_pool* p, bool is_in, uint8_t* img, const Ru
     L.chunk_bytes = p->shape.C;
     L.pool_lstride = (uint64_t)p->shape.N * p->shape.C;
     L.max_workgroups = p->max_wg[target];
-    L.nt_pool_store = aqua::nt_pool_store(p->shape.C, (uint64_t)nl * p->call_blocks * p->shape.C);
+    L.nt_pool_store = aqua::nt_pool_store(p->shape.C, (uint64_t)nl * p->call_blocks * p->shape.C,
+                                          p->call_dealt);
     L.threads = aqua::run_threads(p->call_blocks * p->shape.C / std::max<uint32_t>(1, ndesc),
                                   L.max_workgroups != 0);
     L.xcd_order = false;
@@ -895,12 +897,17 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
     } else {
         aqua::plan_runs(p->shape, a, p->unit_bytes, &p->plan);
     }
+    // Zero-copy kernels are bound by the link, not by HBM: run_order alone.
+    const bool zero_copy = target == AQUA_TARGET_HOST && !staged;
     const aqua::RunOrder order =
-        AQUA_SORT_RUNS ? aqua::run_order(is_in, p->shape.C, total, p->shape.N, num_seqs)
-                       : aqua::RunOrder::kTable;
+        !AQUA_SORT_RUNS ? aqua::RunOrder::kTable
+        : zero_copy     ? aqua::run_order(is_in, p->shape.C, total, p->shape.N, num_seqs)
+                        : aqua::call_order(is_in, p->shape.C, total, p->shape.N, num_seqs,
+                                           (uint64_t)l_count * total * p->shape.C);
     if (order == aqua::RunOrder::kSortedDealt)
         aqua::sort_by_block(&p->plan, p->shape.N, &p->sort_counts, &p->sort_tmp);
     const bool dealt = order != aqua::RunOrder::kTable;
+    p->call_dealt = dealt;
     if (dealt) aqua::interleave_runs(&p->plan, aqua::kXcdWays, &p->sort_tmp);
     aqua::image_ranges(p->shape, a, &p->ranges);
     for (auto& r : p->ranges) {  // tracked by the caller's address of the buffer

@@ -197,6 +197,17 @@ RunOrder run_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t n
     return dense && is_in ? RunOrder::kSortedDealt : RunOrder::kTable;
 }
 
+RunOrder call_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t num_blocks,
+                    uint32_t num_seqs, uint64_t call_bytes) {
+    const RunOrder o = run_order(is_in, chunk_bytes, blocks, num_blocks, num_seqs);
+    if (o != RunOrder::kTable || chunk_bytes >= kDealMinChunk || !num_blocks ||
+        blocks < 2 * kXcdWays)
+        return o;
+    if (!is_in) return RunOrder::kTableDealt;
+    if (call_bytes >= kXcdInMinBytes && xcd_unit_order(chunk_bytes, false)) return o;
+    return blocks * kSortMinShare >= num_blocks ? RunOrder::kSortedDealt : RunOrder::kTableDealt;
+}
+
 void sort_by_block(std::vector<RunDesc>* runs, uint32_t num_blocks,
                    std::vector<uint32_t>* counts, std::vector<RunDesc>* tmp) {
     if ((uint64_t)runs->size() * kSortCountingMinRatio < num_blocks) {

@@ -159,6 +159,27 @@ constexpr uint64_t kDealOutMinMeanBlocks = 32;  // sparse swap-outs: blocks per 
 RunOrder run_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t num_blocks,
                    uint32_t num_seqs);
 
+// run_order refined by the bytes a call of chunks under 64 KiB moves, for the
+// calls that run_order leaves in table order.  With the lanes of run_threads
+// and nontemporal stores (nt_pool_store), dealing pays there too.  Measured on
+// MI355X, 32 layers, one and 16 sequences, a third and an eighth of the pool,
+// cold caches, against table order (and, between 16 and 64 KiB, the XCD unit
+// order) with ordinary scatter stores:
+//   swap-outs, dealt in table order: 128 MiB 0-11 % shorter, 512 MiB 0-24 %
+//     (the 24 % with 16 sequences), 2 GiB 0-8 %; against the XCD unit order
+//     2-14 % at 128 MiB, 0-6 % at 512 MiB, within 3 % from 2 GiB on;
+//   swap-ins, dealt: 128 MiB 5-22 % shorter, 512 MiB 3-25 %; sorted first as
+//     well, another 0-6 % from 512 MiB on, nothing below.  The sort is O(runs +
+//     pool blocks), so only calls that cover a sixteenth of the pool take it.
+//   Swap-ins of 2 GiB and more, chunks between 16 and 64 KiB, a small part of
+//     the pool: the XCD unit order is 2-12 % shorter than sorted and dealt, so
+//     those keep it.
+// The bytes are the whole call's.
+constexpr uint64_t kXcdInMinBytes = 2ull << 30;
+constexpr uint64_t kSortMinShare = 16;  // a sixteenth of the pool's blocks
+RunOrder call_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t num_blocks,
+                    uint32_t num_seqs, uint64_t call_bytes);
+
 // Puts the runs in ascending order of their first block, keeping the table
 // order of runs that start at the same block (a swap-out may name a block
 // twice).  A counting sort over the pool's blocks, O(runs + num_blocks), when

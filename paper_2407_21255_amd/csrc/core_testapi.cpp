@@ -100,6 +100,12 @@ int64_t aqua_core_plan(const aqua_kv_desc* desc, uint32_t num_seqs,
     return (int64_t)plan.size();
 }
 
+int32_t aqua_core_call_order(int32_t is_in, uint64_t chunk_bytes, uint64_t blocks,
+                             uint32_t num_blocks, uint32_t num_seqs, uint64_t call_bytes) {
+    return (int32_t)aqua::call_order(is_in != 0, chunk_bytes, blocks, num_blocks, num_seqs,
+                                     call_bytes);
+}
+
 uint32_t aqua_core_run_threads(uint64_t run_bytes, int32_t capped) {
     return aqua::run_threads(run_bytes, capped != 0);
 }

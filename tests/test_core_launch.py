@@ -19,3 +19,39 @@ def test_lanes_follow_the_mean_run(run_bytes, lanes):
     fn.argtypes, fn.restype = [ctypes.c_uint64, ctypes.c_int32], ctypes.c_uint32
     assert fn(run_bytes, 0) == lanes
     assert fn(run_bytes, 1) == 1024
+
+
+def _order(is_in, chunk, blocks, num_blocks, seqs, nbytes):
+    fn = core_lib.lib().aqua_core_call_order
+    fn.argtypes = [ctypes.c_int32, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32,
+                   ctypes.c_uint32, ctypes.c_uint64]
+    fn.restype = ctypes.c_int32
+    return fn(int(is_in), chunk, blocks, num_blocks, seqs, nbytes)
+
+
+@pytest.mark.parametrize("chunk", [16, 8 * K, 16 * K, 16 * K + 16, 32 * K, 64 * K - 16, 64 * K])
+def test_small_chunk_calls_are_dealt(chunk):
+    """Chunks under 64 KiB: swap-outs dealt, swap-ins dealt and, from a
+    sixteenth of the pool up, sorted; but 2 GiB and more of a small part of
+    the pool in chunks between 16 and 64 KiB stays in table order, which
+    those kernels take in XCD unit order.  64 KiB follows run_order."""
+    T, S, D = core_lib.TABLE, core_lib.SORTED_DEALT, core_lib.TABLE_DEALT
+    G = 1 << 30
+    if chunk == 64 * K:
+        for is_in in (0, 1):
+            for blocks, n, seqs in ((15, 4096, 1), (512, 4096, 64), (2048, 4096, 1)):
+                assert _order(is_in, chunk, blocks, n, seqs, 4 * G) == \
+                    core_lib.run_order(is_in, chunk, blocks, n, seqs)
+        return
+    between = 16 * K < chunk
+    for seqs in (1, 64):
+        assert _order(0, chunk, 15, 4096, seqs, G) == T
+        assert _order(0, chunk, 16, 4096, seqs, G) == D
+        assert _order(0, chunk, 2048, 4096, seqs, 4 * G) == D
+        assert _order(1, chunk, 15, 4096, seqs, G) == T
+        assert _order(1, chunk, 255, 4096, seqs, G) == D
+        assert _order(1, chunk, 256, 4096, seqs, G) == S
+        assert _order(1, chunk, 256, 4096, seqs, 2 * G - 1) == S
+        assert _order(1, chunk, 256, 4096, seqs, 2 * G) == (T if between else S)
+        assert _order(1, chunk, 2048, 4096, seqs, 4 * G) == S
+    assert _order(1, chunk, 0, 0, 0, 0) == T
