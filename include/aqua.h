@@ -236,10 +236,11 @@ AQUA_API aqua_status aqua_swap_in_ex(aqua_kv_pool_t pool, uint32_t num_seqs,
  * event or stream.  (Its host-side planning, like that of the other
  * calls, uses ordinary host memory: the pool's planning buffers, which
  * keep the capacity of the largest call seen, and the sort of a swap-in's
- * runs.)  Its run descriptors go through the pool's pinned ring
+ * runs.)  The run descriptors of a call of at most 224 runs travel in its
+ * kernel's arguments; those of a larger call go through the pool's pinned ring
  * (allocated when the pool was created; the call never grows it) to a
  * device scratch array of 2 MiB that the library holds on each device for
- * the life of the process, and its completion event is one of the 16 the
+ * the life of the process.  The completion event is one of the 16 the
  * pool created.  While none is spare (16 calls of the pool in flight), the
  * call first blocks the host until the oldest outstanding call of the pool
  * has completed; a caller that holds its streams from the host must not
@@ -253,8 +254,8 @@ AQUA_API aqua_status aqua_swap_in_ex(aqua_kv_pool_t pool, uint32_t num_seqs,
  *     slots and copy engines);
  *   - all layers are moved (no layer range or partial image).
  * The scratch array is shared by every pool on a device and keeps the last
- * call's descriptors.  Calls of this entry point on one pool are ordered
- * with each other by the library (they all write the scratch); calls on
+ * descriptors written to it.  Calls of this entry point on one pool are ordered
+ * with each other by the library; calls of more than 224 runs on
  * different pools of one device that may overlap in time race on the
  * scratch and must be ordered by the caller (one stream, or a sync). */
 AQUA_API aqua_status aqua_swap_noalloc(aqua_kv_pool_t pool, int32_t direction,

@@ -116,6 +116,8 @@ struct aqua_kv_pool {
     aqua::DupMarks marks;
     HazardTracker tracker;
     std::vector<RunDesc> plan;
+    aqua::InlineRuns inl;               // the plan of a call of few runs
+    bool call_inline = false;           // the call being enqueued carries its plan so
     std::vector<uint32_t> sort_counts;  // scratch of aqua::sort_by_block
     std::vector<RunDesc> sort_tmp;
     std::vector<std::pair<uint64_t, uint64_t>> ranges;
@@ -599,6 +601,7 @@ aqua::SwapLaunch make_launch(aqua_kv_pool* p, bool is_in, uint8_t* img, const Ru
     L.img = img;
     L.img_l0 = 0;
     L.descs = descs;
+    L.inl = p->call_inline ? &p->inl : nullptr;
     L.ndesc = ndesc;
     L.first_layer = l0;
     L.num_layers = nl;
@@ -918,18 +921,27 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
         (uint64_t)(uintptr_t)p->staging[is_in],
         (uint64_t)(uintptr_t)p->staging[is_in] + 2 * slot};
 
+    // A call of few runs carries them in its kernels' arguments and needs no
+    // descriptor space.
+    p->call_inline = aqua::pack_inline(p->plan, &p->inl);
+
     // Reserve descriptor space before registering the ticket: a reservation
     // may wait on earlier tickets.
     uint64_t ring_off = 0;
-    const uint64_t dbytes = p->plan.size() * sizeof(RunDesc);
+    const uint64_t dbytes = p->call_inline ? 0 : p->plan.size() * sizeof(RunDesc);
     uint64_t waited_ns = 0;
     Outstanding rec{ticket, nullptr, {}};
     // The allocation-free form: descriptors beyond the scratch are refused
     // before anything happens, and the call's event is a recycled one.
     const std::pair<uint64_t, uint64_t> scratch_range{
-        (uint64_t)(uintptr_t)p->scratch, (uint64_t)(uintptr_t)p->scratch + dbytes};
+        (uint64_t)(uintptr_t)p->scratch,
+        (uint64_t)(uintptr_t)p->scratch + p->plan.size() * sizeof(RunDesc)};
     if (noalloc) {
-        if (dbytes > kScratchBytes) return AQUA_ERR_CAPACITY;
+        // The limits hold for every call, also those whose runs travel in the
+        // kernel's arguments.
+        const uint64_t pbytes = p->plan.size() * sizeof(RunDesc);
+        if (pbytes > kScratchBytes || ((pbytes + 255) & ~255ull) > p->ring_bytes)
+            return AQUA_ERR_CAPACITY;
         if (!p->scratch) return AQUA_ERR_HIP;
         const auto w0 = std::chrono::steady_clock::now();
         st = take_event_noalloc(p, &rec.ev);
@@ -957,7 +969,8 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
     // Accesses: swap-out reads the table's blocks and writes the images,
     // swap-in reads the images and writes the blocks; the staged path also
     // writes its slots, and the allocation-free form the device scratch (so
-    // that two such calls on one pool never overlap).
+    // that two such calls on one pool never overlap, which holds for all of
+    // them, also those whose runs travel in the kernel's arguments).
     HazardTracker::Access acc;
     if (is_in) {
         acc.blocks_written = ids;
@@ -967,7 +980,7 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
         if (staged) {
             acc.ranges_written = &stage_range;
             acc.n_ranges_written = 1;
-        } else if (noalloc && dbytes) {
+        } else if (noalloc && !p->plan.empty()) {
             acc.ranges_written = &scratch_range;
             acc.n_ranges_written = 1;
         }
@@ -975,7 +988,7 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
         acc.blocks_read = ids;
         acc.n_blocks_read = (size_t)total;
         if (staged) p->ranges.push_back(stage_range);
-        if (noalloc && dbytes) p->ranges.push_back(scratch_range);
+        if (noalloc && !p->plan.empty()) p->ranges.push_back(scratch_range);
         acc.ranges_written = p->ranges.data();
         acc.n_ranges_written = p->ranges.size();
     }
@@ -990,18 +1003,21 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
         p->stats.waits_inserted++;
     }
 
-    if (dbytes) {
-        std::memcpy(p->ring_host + ring_off, p->plan.data(), dbytes);
+    if (!p->plan.empty()) {
         hipError_t e = hipSuccess;
-        const uint8_t* descs = p->ring_host_dev + ring_off;
-        if (noalloc) {
-            descs = p->scratch;
-            e = upload_to(p->ring_host_dev + ring_off, p->scratch, dbytes, stream);
-        } else if (staged || AQUA_DESC_DEVICE) {
-            descs = p->ring_dev + ring_off;
-            e = upload_descs(p, ring_off, dbytes, stream);
+        const uint8_t* descs = nullptr;
+        if (dbytes) {
+            std::memcpy(p->ring_host + ring_off, p->plan.data(), dbytes);
+            descs = p->ring_host_dev + ring_off;
+            if (noalloc) {
+                descs = p->scratch;
+                e = upload_to(p->ring_host_dev + ring_off, p->scratch, dbytes, stream);
+            } else if (staged || AQUA_DESC_DEVICE) {
+                descs = p->ring_dev + ring_off;
+                e = upload_descs(p, ring_off, dbytes, stream);
+            }
+            if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
         }
-        if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
         if (staged) {
             st = enqueue_staged(p, is_in, buf, stream, reinterpret_cast<const RunDesc*>(descs),
                                 (uint32_t)p->plan.size(), slot, G, l_begin, l_begin + l_count,

@@ -170,6 +170,17 @@ size_t plan_runs(const Shape& s, const CallArgs& a, uint64_t max_unit_bytes,
     return out->size() - before;
 }
 
+bool pack_inline(const std::vector<RunDesc>& runs, InlineRuns* out) {
+    if (runs.size() > kInlineRuns) return false;
+    InlineRun* o = out->run;
+    for (const RunDesc& r : runs) {
+        const uint64_t off = r.img_off / 16, ls = r.img_lstride / 16;
+        if (off > UINT32_MAX || ls > UINT32_MAX) return false;
+        *o++ = {r.block, r.nchunks, (uint32_t)off, (uint32_t)ls};
+    }
+    return true;
+}
+
 uint32_t swap_threads(uint64_t chunk_bytes, uint32_t min_threads) {
     uint32_t lo = 64;
     while (lo < min_threads && lo < kMaxThreads) lo *= 2;

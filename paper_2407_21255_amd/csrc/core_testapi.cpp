@@ -106,6 +106,18 @@ int32_t aqua_core_call_order(int32_t is_in, uint64_t chunk_bytes, uint64_t block
                                      call_bytes);
 }
 
+// Packs n 32-byte runs for a kernel's arguments and unpacks them into `out`;
+// 0 if they do not go there.
+int32_t aqua_core_inline_round_trip(const void* descs, uint64_t n, void* out) {
+    std::vector<aqua::RunDesc> runs(n);
+    if (n) std::memcpy(runs.data(), descs, n * sizeof(aqua::RunDesc));
+    aqua::InlineRuns packed;
+    if (!aqua::pack_inline(runs, &packed)) return 0;
+    for (uint64_t k = 0; k < n; ++k)
+        static_cast<aqua::RunDesc*>(out)[k] = aqua::unpack_inline(packed.run[k]);
+    return 1;
+}
+
 uint32_t aqua_core_run_threads(uint64_t run_bytes, int32_t capped) {
     return aqua::run_threads(run_bytes, capped != 0);
 }

@@ -14,7 +14,8 @@ struct SwapLaunch {
     uint8_t* pool;            // device pointer of the pool base
     uint8_t* img;             // device-accessible pointer of the buffer base
     uint32_t img_l0;          // layer l's image data starts at img_off + (l - img_l0) * lstride
-    const RunDesc* descs;     // device copy of the run descriptors
+    const RunDesc* descs;     // device-accessible run descriptors
+    const InlineRuns* inl;    // if not null: the runs, passed as a kernel argument instead
     uint32_t ndesc;
     uint32_t first_layer;     // layers [first_layer, first_layer + num_layers)
     uint32_t num_layers;

