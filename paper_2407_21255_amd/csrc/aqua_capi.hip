@@ -30,6 +30,13 @@ constexpr uint64_t kDefaultRingBytes = 4ull << 20;  // 131072 descriptors
 constexpr uint64_t kDefaultUnitBytes = 64ull << 10;
 constexpr uint64_t kDefaultSlotBytes = 512ull << 20;  // staged path, per slot
 constexpr uint32_t kHostZeroCopyWorkgroups = 16;
+// A call's completion event rides on its kernel's launch (launch_swap), but on
+// every 32nd call it is recorded behind the kernel: the runtime retires its
+// finished launches where it meets such a packet.  Without any, 20000 calls
+// issued with no sync left 12 ms of that work behind, which slowed the
+// process's next HIP calls (a 1 us allocation took 5 us); with one in 32 none
+// was left, at 0.1-0.2 us per call.
+constexpr uint64_t kRecordEvery = 32;
 
 // Measurement switches: the defaults are the shipped configuration, the
 // macros exist so that sweeps can build variants.
@@ -1003,6 +1010,7 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
         p->stats.waits_inserted++;
     }
 
+    bool recorded = false;  // the call's event is on its kernel
     if (!p->plan.empty()) {
         hipError_t e = hipSuccess;
         const uint8_t* descs = nullptr;
@@ -1032,15 +1040,23 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
                 make_launch(p, is_in, dbuf, reinterpret_cast<const RunDesc*>(descs),
                             (uint32_t)p->plan.size(), target, l_begin, l_count);
             L.xcd_order = target == AQUA_TARGET_DEVICE && aqua::xcd_unit_order(p->shape.C, dealt);
-            (void)hipGetLastError();
-            e = aqua::launch_swap(L, stream, &p->stats.launches);
+            recorded = ticket % kRecordEvery != 0;
+            if (recorded && !rec.ev) e = take_event(p, &rec.ev);
             if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
+            (void)hipGetLastError();
+            e = aqua::launch_swap(L, stream, &p->stats.launches, recorded ? rec.ev : nullptr);
+            if (e != hipSuccess) {
+                give_back();
+                return fail_enqueued(stream, latch(p, e));
+            }
         }
     }
 
-    hipError_t e = rec.ev ? hipSuccess : take_event(p, &rec.ev);
-    if (e == hipSuccess) e = hipEventRecord(rec.ev, stream);
-    if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
+    if (!recorded) {
+        hipError_t e = rec.ev ? hipSuccess : take_event(p, &rec.ev);
+        if (e == hipSuccess) e = hipEventRecord(rec.ev, stream);
+        if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
+    }
     p->outstanding[lane].push_back(std::move(rec));
     if (dbytes) p->ring_uses.push_back({ring_off, ring_off + ((dbytes + 255) & ~255ull), ticket});
 

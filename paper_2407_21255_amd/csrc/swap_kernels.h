@@ -51,8 +51,15 @@ inline bool nt_pool_store(uint64_t chunk_bytes, uint64_t call_bytes, bool dealt)
 }
 
 // Enqueues the copy on `stream`; returns the first launch error.  Adds the
-// number of kernel launches it made to *launches when that is given.
-hipError_t launch_swap(const SwapLaunch& a, hipStream_t stream, uint64_t* launches = nullptr);
+// number of kernel launches it made to *launches when that is given.  `done`,
+// if given, completes with the last launch: the launch itself carries it
+// (hipExtLaunchKernel), or, while the stream is being captured, a record after
+// it does.  A record is a packet of its own behind the kernel; measured on
+// MI355X, back-to-back calls with the event on the launch took 2.5-2.8 us less
+// each (8 MiB 7.5 -> 5.0 us, 32 MiB 15.0 -> 12.3 us), 0.5 us of them host time,
+// and a wait for the event ended 2.4 us earlier.
+hipError_t launch_swap(const SwapLaunch& a, hipStream_t stream, uint64_t* launches = nullptr,
+                       hipEvent_t done = nullptr);
 
 // Enqueues one HBM yardstick over `bytes` (a multiple of 16) of device
 // memory with the swap kernels' copy loop: mode 0 copies src to dst, mode 1

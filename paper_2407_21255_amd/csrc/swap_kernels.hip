@@ -16,6 +16,7 @@
 // the scatter's pool stores are nontemporal for chunks of 64 KiB and more
 // and for calls that write 2 GiB or more, where that measured faster, and
 // ordinary otherwise (nt_pool_store).
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -214,9 +215,22 @@ __global__ __launch_bounds__(kMaxThreads) void yardstick_kernel(
     }
 }
 
+// One launch; `done`, if given, completes with it (see launch_swap).
+hipError_t launch_with_event(const void* fn, uint32_t grid, uint32_t threads, void** args,
+                             hipStream_t stream, hipEvent_t done) {
+    if (!done) return hipLaunchKernel(fn, dim3(grid), dim3(threads), args, 0, stream);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone)
+        return hipExtLaunchKernel(fn, dim3(grid), dim3(threads), args, 0, stream, nullptr, done,
+                                  0);
+    (void)hipGetLastError();
+    const hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(threads), args, 0, stream);
+    return e == hipSuccess ? hipEventRecord(done, stream) : e;
+}
+
 template <bool OUT, bool NT_POOL_ST, int THREADS>
 hipError_t launch_swap_k(const SwapLaunch& a, uint32_t grid, uint32_t l0, uint32_t units,
-                         hipStream_t stream) {
+                         hipStream_t stream, hipEvent_t done) {
     // The argument array hands the runtime the runs where they are; passed by
     // value they would be copied once more.  The shorter argument is a prefix
     // of the longer one.
@@ -231,15 +245,16 @@ hipError_t launch_swap_k(const SwapLaunch& a, uint32_t grid, uint32_t l0, uint32
     else if (a.inl)
         fn = reinterpret_cast<const void*>(
             &swap_runs_inline_kernel<OUT, NT_POOL_ST, THREADS, kInlineRuns>);
-    return hipLaunchKernel(fn, dim3(grid), dim3(THREADS), const_cast<void**>(args), 0, stream);
+    return launch_with_event(fn, grid, THREADS, const_cast<void**>(args), stream, done);
 }
 
 template <int THREADS>
 hipError_t launch_swap_t(const SwapLaunch& a, uint32_t grid, uint32_t l0, uint32_t units,
-                         hipStream_t stream) {
-    if (a.out) return launch_swap_k<true, false, THREADS>(a, grid, l0, units, stream);
-    if (a.nt_pool_store) return launch_swap_k<false, true, THREADS>(a, grid, l0, units, stream);
-    return launch_swap_k<false, false, THREADS>(a, grid, l0, units, stream);
+                         hipStream_t stream, hipEvent_t done) {
+    if (a.out) return launch_swap_k<true, false, THREADS>(a, grid, l0, units, stream, done);
+    if (a.nt_pool_store)
+        return launch_swap_k<false, true, THREADS>(a, grid, l0, units, stream, done);
+    return launch_swap_k<false, false, THREADS>(a, grid, l0, units, stream, done);
 }
 
 }  // namespace
@@ -252,8 +267,9 @@ hipError_t launch_copy(const uint8_t* src, uint8_t* dst, const CopyDesc* descs, 
     return hipGetLastError();
 }
 
-hipError_t launch_swap(const SwapLaunch& a, hipStream_t stream, uint64_t* launches) {
-    if (!a.ndesc || !a.num_layers) return hipSuccess;
+hipError_t launch_swap(const SwapLaunch& a, hipStream_t stream, uint64_t* launches,
+                       hipEvent_t done) {
+    if (!a.ndesc || !a.num_layers) return done ? hipEventRecord(done, stream) : hipSuccess;
     // Whole layers per launch, fewer than 2^31 units each.
     const uint32_t per = layers_per_launch(a.ndesc);
     const uint32_t end = a.first_layer + a.num_layers;
@@ -261,13 +277,14 @@ hipError_t launch_swap(const SwapLaunch& a, hipStream_t stream, uint64_t* launch
         const uint32_t nl = std::min<uint32_t>(per, end - l0);
         const uint32_t units = nl * a.ndesc;
         const uint32_t grid = launch_grid(units, a.max_workgroups);
+        const hipEvent_t last = l0 + nl == end ? done : nullptr;
         hipError_t e = hipErrorInvalidValue;
         switch (a.threads) {
-            case 1024: e = launch_swap_t<1024>(a, grid, l0, units, stream); break;
-            case 512: e = launch_swap_t<512>(a, grid, l0, units, stream); break;
-            case 256: e = launch_swap_t<256>(a, grid, l0, units, stream); break;
-            case 128: e = launch_swap_t<128>(a, grid, l0, units, stream); break;
-            case 64: e = launch_swap_t<64>(a, grid, l0, units, stream); break;
+            case 1024: e = launch_swap_t<1024>(a, grid, l0, units, stream, last); break;
+            case 512: e = launch_swap_t<512>(a, grid, l0, units, stream, last); break;
+            case 256: e = launch_swap_t<256>(a, grid, l0, units, stream, last); break;
+            case 128: e = launch_swap_t<128>(a, grid, l0, units, stream, last); break;
+            case 64: e = launch_swap_t<64>(a, grid, l0, units, stream, last); break;
             default: break;
         }
         if (e != hipSuccess) return e;

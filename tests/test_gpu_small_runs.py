@@ -126,3 +126,39 @@ def test_ring_wraps_under_calls_that_need_it(monkeypatch, where):
         assert_bytes_equal(host(img), want, "image")
         assert oracle.swap_in(d, pool_h, [[b + 1 for b in t]], want) == 0
     assert_bytes_equal(host(pool), pool_h, "pool")
+
+
+@pytest.mark.parametrize("runs", [20, 150, 240])
+@pytest.mark.parametrize("entry", ["out", "noalloc"])
+def test_one_call_captured_and_replayed(entry, runs):
+    """One call captured into a HIP graph (its event is then recorded, not
+    carried by the launch), replayed four times over changing pool bytes with
+    eager work and a sync in between: every replay equals the gather."""
+    shape = wl.KVShape(3, 512, 1, 16, 64, wl.BF16)             # 4 KiB chunks
+    pool = device_pool(shape, 43)
+    table = [2 * b for b in wl.permutation(shape.num_blocks // 2, 43)[:runs]]
+    idx = torch.tensor(table, device="cuda")
+    img = torch.zeros(shape.image_bytes(runs), dtype=torch.uint8, device="cuda")
+    kv = aqua.KVPool(shape.as_tuple(), pool)
+
+    def call():
+        s = torch.cuda.current_stream()
+        return kv.swap_out([table], img, stream=s) if entry == "out" else \
+            kv.swap_noalloc(0, [table], img, stream=s)
+
+    try:
+        call()
+        kv.sync()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+            call()
+        for k in range(4):
+            say(entry, runs, "replay", k)
+            img.zero_()
+            pool.add_(1)
+            graph.replay()
+            torch.cuda.synchronize()
+            want = pool.view(3, 512, -1)[:, idx].reshape(-1)
+            assert torch.equal(img, want), k
+    finally:
+        kv.close()
