@@ -124,6 +124,7 @@ struct aqua_kv_pool {
     HazardTracker tracker;
     std::vector<RunDesc> plan;
     aqua::InlineRuns inl;               // the plan of a call of few runs
+    aqua::InlineRanges inl_ranges;      // the ranges of a migration of few
     bool call_inline = false;           // the call being enqueued carries its plan so
     std::vector<uint32_t> sort_counts;  // scratch of aqua::sort_by_block
     std::vector<RunDesc> sort_tmp;
@@ -518,8 +519,10 @@ hipError_t warm_kernels(aqua_kv_pool* p) {
     hipStream_t s = nullptr;
     hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
     if (e != hipSuccess) return e;
-    e = aqua::launch_copy(p->base, p->base,
-                              reinterpret_cast<const aqua::CopyDesc*>(p->ring_host_dev), 1, 0, s);
+    e = aqua::launch_copy({p->base, p->base,
+                           reinterpret_cast<const aqua::CopyDesc*>(p->ring_host_dev), nullptr, 0,
+                           1, 0},
+                          s);
     if (e == hipSuccess) e = upload_descs(p, 0, 32, s);
     if (e == hipSuccess)
         e = aqua::launch_release_flags(reinterpret_cast<int64_t*>(p->ring_dev + 64), nullptr, s);
@@ -1130,8 +1133,20 @@ aqua_status do_migrate(aqua_kv_pool* p, const void* src, uint64_t src_bytes, int
     const uint32_t lane = lane_for(p, stream);
     const uint64_t ticket = p->next_ticket;
 
+    // Few ranges travel in the kernel's arguments; more go piece by piece
+    // through the rings.
     std::vector<aqua::CopyDesc> pieces;
-    if (!engine) aqua::plan_copies(n, so, dof, len, kDefaultUnitBytes, &pieces);
+    aqua::CopyLaunch L{dsrc, ddst, nullptr, nullptr, 0, 0, 0};
+    if (!engine && moved) {
+        const uint64_t total = aqua::pack_ranges(n, so, dof, len, &p->inl_ranges, &L.ranges);
+        if (L.ranges <= aqua::kInlineRanges && total <= UINT32_MAX) {
+            L.inl = &p->inl_ranges;
+            L.pieces = (uint32_t)total;
+        } else {
+            aqua::plan_copies(n, so, dof, len, aqua::kCopyPiece, &pieces);
+            L.pieces = (uint32_t)pieces.size();
+        }
+    }
     p->ranges.clear();
     std::vector<std::pair<uint64_t, uint64_t>> wr;
     for (uint32_t k = 0; k < n; ++k) {
@@ -1185,20 +1200,24 @@ aqua_status do_migrate(aqua_kv_pool* p, const void* src, uint64_t src_bytes, int
         // Descriptors go to the device ring: a migration touching host
         // memory keeps the link busy.
         std::memcpy(p->ring_host + ring_off, pieces.data(), dbytes);
-        hipError_t e = upload_descs(p, ring_off, dbytes, stream);
+        const hipError_t e = upload_descs(p, ring_off, dbytes, stream);
         if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
-        const bool host_side = src_target == AQUA_TARGET_HOST || dst_target == AQUA_TARGET_HOST;
-        (void)hipGetLastError();
-        e = aqua::launch_copy(dsrc, ddst,
-                              reinterpret_cast<const aqua::CopyDesc*>(p->ring_dev + ring_off),
-                              (uint32_t)pieces.size(),
-                              host_side ? p->max_wg[AQUA_TARGET_HOST] : p->max_wg[AQUA_TARGET_DEVICE],
-                              stream);
-        if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
+        L.descs = reinterpret_cast<const aqua::CopyDesc*>(p->ring_dev + ring_off);
     }
     hipError_t e = take_event(p, &rec.ev);
-    if (e == hipSuccess) e = hipEventRecord(rec.ev, stream);
     if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
+    const bool recorded = L.pieces && ticket % kRecordEvery != 0;
+    if (L.pieces) {
+        const bool host_side = src_target == AQUA_TARGET_HOST || dst_target == AQUA_TARGET_HOST;
+        L.max_workgroups = p->max_wg[host_side ? AQUA_TARGET_HOST : AQUA_TARGET_DEVICE];
+        (void)hipGetLastError();
+        e = aqua::launch_copy(L, stream, recorded ? rec.ev : nullptr);
+    }
+    if (e == hipSuccess && !recorded) e = hipEventRecord(rec.ev, stream);
+    if (e != hipSuccess) {
+        p->spare_events.push_back(rec.ev);
+        return fail_enqueued(stream, latch(p, e));
+    }
     p->outstanding[lane].push_back(std::move(rec));
     if (dbytes) p->ring_uses.push_back({ring_off, ring_off + ((dbytes + 255) & ~255ull), ticket});
     p->stats.calls_migrate++;

@@ -304,10 +304,23 @@ size_t plan_copies(uint32_t n, const uint64_t* src_off, const uint64_t* dst_off,
             d.src_off = src_off[k] + o;
             d.dst_off = dst_off[k] + o;
             d.len = std::min<uint64_t>(unit, len[k] - o);
-            d.reserved = 0;
+            d.first_piece = 0;
             out->push_back(d);
         }
     return out->size() - before;
+}
+
+uint64_t pack_ranges(uint32_t n, const uint64_t* src_off, const uint64_t* dst_off,
+                     const uint64_t* len, InlineRanges* out, uint32_t* count) {
+    uint64_t pieces = 0;
+    *count = 0;
+    for (uint32_t k = 0; k < n; ++k) {
+        if (!len[k]) continue;
+        if (++*count > kInlineRanges) return 0;
+        out->range[*count - 1] = {src_off[k], dst_off[k], len[k], pieces};
+        pieces += (len[k] + kCopyPiece - 1) / kCopyPiece;
+    }
+    return pieces;
 }
 
 // ---------------------------------------------------------------------------

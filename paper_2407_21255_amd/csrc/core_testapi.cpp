@@ -118,6 +118,33 @@ int32_t aqua_core_inline_round_trip(const void* descs, uint64_t n, void* out) {
     return 1;
 }
 
+// The pieces of a packed range copy, as (src_off, dst_off, len, index) each;
+// -1 when the ranges are too many to pack.
+int64_t aqua_core_packed_pieces(uint32_t n, const uint64_t* so, const uint64_t* dof,
+                                const uint64_t* len, void* out, uint64_t max_out) {
+    aqua::InlineRanges r;
+    uint32_t count = 0;
+    const uint64_t pieces = aqua::pack_ranges(n, so, dof, len, &r, &count);
+    if (count > aqua::kInlineRanges) return -1;
+    for (uint64_t u = 0; u < pieces && u < max_out; ++u)
+        static_cast<aqua::CopyDesc*>(out)[u] = aqua::piece_of(r, count, u);
+    return (int64_t)pieces;
+}
+
+// Writes up to max_out pieces of the general plan and returns their number.
+int64_t aqua_core_plan_copies(uint32_t n, const uint64_t* so, const uint64_t* dof,
+                              const uint64_t* len, void* out, uint64_t max_out) {
+    std::vector<aqua::CopyDesc> v;
+    aqua::plan_copies(n, so, dof, len, aqua::kCopyPiece, &v);
+    const uint64_t m = v.size() < max_out ? v.size() : max_out;
+    if (m) std::memcpy(out, v.data(), m * sizeof(aqua::CopyDesc));
+    return (int64_t)v.size();
+}
+
+uint32_t aqua_core_xcd_window_unit(uint32_t block, uint32_t units) {
+    return aqua::xcd_window_unit(block, units);
+}
+
 uint32_t aqua_core_run_threads(uint64_t run_bytes, int32_t capped) {
     return aqua::run_threads(run_bytes, capped != 0);
 }

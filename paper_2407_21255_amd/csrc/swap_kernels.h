@@ -67,9 +67,18 @@ hipError_t launch_swap(const SwapLaunch& a, hipStream_t stream, uint64_t* launch
 hipError_t launch_yardstick(int mode, const uint8_t* src, uint8_t* dst, uint64_t bytes,
                             uint32_t key, hipStream_t stream);
 
-// Enqueues the range copy of `n` pieces (each at most 64 KiB, 16-byte
-// multiples) from `src` to `dst`, both device-accessible addresses.
-hipError_t launch_copy(const uint8_t* src, uint8_t* dst, const CopyDesc* descs, uint32_t n,
-                       uint32_t max_workgroups, hipStream_t stream);
+// A range copy between two device-accessible addresses, in 64 KiB pieces.
+struct CopyLaunch {
+    const uint8_t* src;
+    uint8_t* dst;
+    const CopyDesc* descs;    // device-accessible, one per piece
+    const InlineRanges* inl;  // if not null: the ranges, passed as a kernel argument instead
+    uint32_t ranges;          // in *inl
+    uint32_t pieces;
+    uint32_t max_workgroups;  // 0: one workgroup per piece
+};
+
+// Enqueues it on `stream`; `done` as for launch_swap.
+hipError_t launch_copy(const CopyLaunch& a, hipStream_t stream, hipEvent_t done = nullptr);
 
 }  // namespace aqua

@@ -162,16 +162,31 @@ __global__ __launch_bounds__(THREADS) void swap_runs_inline_kernel(
 }
 
 // Range copy between two offload buffers (image migration): work unit u
-// copies descs[u].len bytes from src + src_off to dst + dst_off.
-__global__ __launch_bounds__(kMaxThreads) void copy_ranges_kernel(
-    const uint8_t* __restrict__ src, uint8_t* __restrict__ dst,
-    const CopyDesc* __restrict__ descs, uint32_t n) {
-    for (uint32_t u = blockIdx.x; u < n; u += gridDim.x) {
-        const CopyDesc dsc = descs[u];
+// copies piece get(u).  With one workgroup per piece the XCDs take windows of
+// adjacent pieces (xcd_window_unit); a capped grid loops in plain order.
+template <typename Get>
+__device__ __forceinline__ void copy_pieces(const uint8_t* __restrict__ src,
+                                            uint8_t* __restrict__ dst, const Get& get,
+                                            uint32_t n) {
+    const uint32_t u0 = gridDim.x == n ? xcd_window_unit(blockIdx.x, n) : blockIdx.x;
+    for (uint32_t u = u0; u < n; u += gridDim.x) {
+        const CopyDesc dsc = get(u);
         copy_span<kMaxThreads, true, true>(reinterpret_cast<const v4u*>(src + dsc.src_off),
                                            reinterpret_cast<v4u*>(dst + dsc.dst_off),
                                            (uint32_t)(dsc.len / 16));
     }
+}
+
+__global__ __launch_bounds__(kMaxThreads) void copy_ranges_kernel(
+    const uint8_t* __restrict__ src, uint8_t* __restrict__ dst,
+    const CopyDesc* __restrict__ descs, uint32_t n) {
+    copy_pieces(src, dst, [&](uint32_t u) { return descs[u]; }, n);
+}
+
+__global__ __launch_bounds__(kMaxThreads) void copy_ranges_inline_kernel(
+    const uint8_t* __restrict__ src, uint8_t* __restrict__ dst, const InlineRanges ranges,
+    uint32_t count, uint32_t n) {
+    copy_pieces(src, dst, [&](uint32_t u) { return piece_of(ranges, count, u); }, n);
 }
 
 // HBM yardsticks over nvec contiguous vectors, in 64 KiB pieces with the
@@ -259,12 +274,15 @@ hipError_t launch_swap_t(const SwapLaunch& a, uint32_t grid, uint32_t l0, uint32
 
 }  // namespace
 
-hipError_t launch_copy(const uint8_t* src, uint8_t* dst, const CopyDesc* descs, uint32_t n,
-                       uint32_t max_workgroups, hipStream_t stream) {
-    if (!n) return hipSuccess;
-    hipLaunchKernelGGL(copy_ranges_kernel, dim3(launch_grid(n, max_workgroups)),
-                       dim3(kMaxThreads), 0, stream, src, dst, descs, n);
-    return hipGetLastError();
+hipError_t launch_copy(const CopyLaunch& a, hipStream_t stream, hipEvent_t done) {
+    if (!a.pieces) return done ? hipEventRecord(done, stream) : hipSuccess;
+    const uint32_t grid = launch_grid(a.pieces, a.max_workgroups);
+    const void* inl[] = {&a.src, &a.dst, a.inl, &a.ranges, &a.pieces};
+    const void* ring[] = {&a.src, &a.dst, &a.descs, &a.pieces};
+    const void* fn = a.inl ? reinterpret_cast<const void*>(&copy_ranges_inline_kernel)
+                           : reinterpret_cast<const void*>(&copy_ranges_kernel);
+    return launch_with_event(fn, grid, kMaxThreads, const_cast<void**>(a.inl ? inl : ring), stream,
+                             done);
 }
 
 hipError_t launch_swap(const SwapLaunch& a, hipStream_t stream, uint64_t* launches,

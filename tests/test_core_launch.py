@@ -86,3 +86,45 @@ def test_runs_in_kernel_arguments_keep_every_field(n):
             e = d.copy()
             e[f][n // 2] = top
             assert fits(e) == 0
+
+
+@pytest.mark.parametrize("n", [0, 1, 2, 63, 64, 65, 80])
+def test_packed_ranges_give_the_planned_pieces(n):
+    """The pieces that workgroups find in the packed ranges are those of the
+    general plan, in order, empty ranges left out; more than 64 non-empty
+    ranges are not packed."""
+    L = core_lib.lib()
+    U64 = ctypes.c_uint64
+    for fn in (L.aqua_core_packed_pieces, L.aqua_core_plan_copies):
+        fn.argtypes = [ctypes.c_uint32] + [ctypes.c_void_p] * 4 + [U64]
+        fn.restype = ctypes.c_int64
+    rng = np.random.default_rng(n)
+    sizes = (0, 16, 65520, 65536, 65552, 131072, 1 << 20, 700000 // 16 * 16)
+    for trial in range(20):
+        ln = rng.choice(sizes, n).astype(np.uint64)
+        if trial == 0:
+            ln[:] = 65536
+        so, do = (rng.integers(0, 1 << 40, n).astype(np.uint64) * 16 for _ in range(2))
+        a, b = np.zeros((4096, 4), np.uint64), np.zeros((4096, 4), np.uint64)
+        args = (n, so.ctypes.data, do.ctypes.data, ln.ctypes.data)
+        got = L.aqua_core_packed_pieces(*args, a.ctypes.data, 4096)
+        want = L.aqua_core_plan_copies(*args, b.ctypes.data, 4096)
+        if np.count_nonzero(ln) > 64:
+            assert got == -1
+            continue
+        assert got == want <= 4096
+        assert np.array_equal(a[:got, :3], b[:got, :3])
+        assert np.array_equal(a[:got, 3], np.arange(got, dtype=np.uint64))
+
+
+@pytest.mark.parametrize("units", [0, 1, 7, 8, 9, 63, 64, 65, 127, 128, 200, 20672])
+def test_copy_windows_are_a_bijection(units):
+    """Every piece once; within a window of 64 XCD x (= block % 8) takes the
+    x-th stretch of adjacent pieces."""
+    fn = core_lib.lib().aqua_core_xcd_window_unit
+    fn.argtypes, fn.restype = [ctypes.c_uint32] * 2, ctypes.c_uint32
+    got = [fn(b, units) for b in range(units)]
+    assert sorted(got) == list(range(units))
+    for base in range(0, units - 63, 64):
+        for x in range(8):
+            assert got[base + x:base + 64:8] == list(range(base + 8 * x, base + 8 * x + 8))

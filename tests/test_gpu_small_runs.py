@@ -162,3 +162,40 @@ def test_one_call_captured_and_replayed(entry, runs):
             assert torch.equal(img, want), k
     finally:
         kv.close()
+
+
+@pytest.mark.parametrize("where", ["hbm", "hbm_capped", "host"])
+@pytest.mark.parametrize("n", [1, 9, 64, 65, 130])
+def test_range_copies_of_few_and_many_ranges(n, where):
+    """Migrations by the range-copy kernel at and beside the number of ranges
+    its arguments hold: ragged ranges of 0 bytes to 1.5 MiB, in another order
+    at the destination, with gaps that must not change."""
+    rng = np.random.default_rng(n)
+    sizes = (0, 16, 48, 4096, 65520, 65536, 65552, 200000, 1 << 20, 1500000)
+    ln = rng.choice(sizes, n).astype(np.uint64) // 16 * 16
+    ln[0] = 327696
+    so = np.concatenate([[32], 32 + np.cumsum(ln + 64)[:-1]]).astype(np.uint64)
+    total = int((ln + 64).sum()) + 64
+    do, at = np.zeros(n, np.uint64), 16
+    for k in rng.permutation(n):
+        do[k] = at
+        at += int(ln[k]) + 32
+    src_h = rng.integers(0, 256, total, dtype=np.uint8)
+    want = np.full(total, wl.GUARD_BYTE, dtype=np.uint8)
+    for s, d, m in zip(so.astype(int), do.astype(int), ln.astype(int)):
+        want[d:d + m] = src_h[s:s + m]
+    src, dst = torch.from_numpy(src_h), torch.from_numpy(np.full_like(want, wl.GUARD_BYTE))
+    src, dst = (src.pin_memory(), dst.pin_memory()) if where == "host" else (src.cuda(), dst.cuda())
+    shape = wl.KVShape(2, 16, 1, 2, 8, wl.BF16)
+    pool = device_pool(shape, 47)
+    kv = aqua.KVPool(shape.as_tuple(), pool)
+    try:
+        if where == "hbm_capped":
+            kv.set_max_workgroups(aqua.AQUA_TARGET_DEVICE, 7)
+        say(where, "ranges", n, "bytes", int(ln.sum()))
+        kv.migrate(src, dst, so, do, ln)
+        kv.sync()
+        assert kv.stats()["bytes_migrated"] == int(ln.sum())
+    finally:
+        kv.close()
+    assert_bytes_equal(host(dst), want, "destination and gaps")
