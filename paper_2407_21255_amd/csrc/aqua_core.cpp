@@ -214,9 +214,9 @@ RunOrder call_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t 
     if (o != RunOrder::kTable || chunk_bytes >= kDealMinChunk || !num_blocks ||
         blocks < 2 * kXcdWays)
         return o;
-    if (!is_in) return RunOrder::kTableDealt;
-    if (call_bytes >= kXcdInMinBytes && xcd_unit_order(chunk_bytes, false)) return o;
-    return blocks * kSortMinShare >= num_blocks ? RunOrder::kSortedDealt : RunOrder::kTableDealt;
+    if (call_bytes >= kXcdUnitMinBytes && xcd_unit_order(chunk_bytes, false)) return o;
+    const bool sorted = is_in && blocks * kSortMinShare >= num_blocks;
+    return sorted ? RunOrder::kSortedDealt : RunOrder::kTableDealt;
 }
 
 void sort_by_block(std::vector<RunDesc>* runs, uint32_t num_blocks,

@@ -39,12 +39,14 @@ struct SwapLaunch {
 // 2-15 % longer.
 // Runs dealt out to the XCDs turn the smaller calls round: each XCD then
 // writes one contiguous stretch of a layer.  Dealt scatters of 2 to 32 KiB
-// chunks, cold caches, nontemporal against ordinary stores: 64 MiB 6-10 %
-// shorter, 128 MiB 11-13 %, 256 MiB to 1 GiB 10-16 %; 32 MiB within 6 % either
-// way, 8 MiB 9-13 % longer, hence the 32 MiB.
+// chunks, nontemporal against ordinary stores: 256 MiB to 1 GiB 10-16 %
+// shorter.  Below the 256 MB of the last-level cache it depends on what
+// follows: one call after another, 64 MiB 6-10 % and 128 MiB 11-13 % shorter;
+// a call by itself, whose stores the cache absorbs, 8-14 % longer (198 MiB 99
+// against 86 us).  Those keep ordinary stores.
 constexpr uint64_t kNtPoolStoreMinChunk = 64ull << 10;
 constexpr uint64_t kNtPoolStoreMinBytes = 2ull << 30;
-constexpr uint64_t kNtPoolStoreMinDealt = 32ull << 20;
+constexpr uint64_t kNtPoolStoreMinDealt = 256ull << 20;
 inline bool nt_pool_store(uint64_t chunk_bytes, uint64_t call_bytes, bool dealt) {
     return chunk_bytes >= kNtPoolStoreMinChunk || call_bytes >= kNtPoolStoreMinBytes ||
            (dealt && call_bytes >= kNtPoolStoreMinDealt);

@@ -33,9 +33,9 @@ def _order(is_in, chunk, blocks, num_blocks, seqs, nbytes):
 @pytest.mark.parametrize("chunk", [16, 8 * K, 16 * K, 16 * K + 16, 32 * K, 64 * K - 16, 64 * K])
 def test_small_chunk_calls_are_dealt(chunk):
     """Chunks under 64 KiB: swap-outs dealt, swap-ins dealt and, from a
-    sixteenth of the pool up, sorted; but 2 GiB and more of a small part of
-    the pool in chunks between 16 and 64 KiB stays in table order, which
-    those kernels take in XCD unit order.  64 KiB follows run_order."""
+    sixteenth of the pool up, sorted; but 2 GiB and more in chunks between 16
+    and 64 KiB (swap-ins: of a small part of the pool) stays in table order,
+    which those kernels take in XCD unit order.  64 KiB follows run_order."""
     T, S, D = core_lib.TABLE, core_lib.SORTED_DEALT, core_lib.TABLE_DEALT
     G = 1 << 30
     if chunk == 64 * K:
@@ -48,7 +48,8 @@ def test_small_chunk_calls_are_dealt(chunk):
     for seqs in (1, 64):
         assert _order(0, chunk, 15, 4096, seqs, G) == T
         assert _order(0, chunk, 16, 4096, seqs, G) == D
-        assert _order(0, chunk, 2048, 4096, seqs, 4 * G) == D
+        assert _order(0, chunk, 2048, 4096, seqs, 2 * G - 1) == D
+        assert _order(0, chunk, 2048, 4096, seqs, 2 * G) == (T if between else D)
         assert _order(1, chunk, 15, 4096, seqs, G) == T
         assert _order(1, chunk, 255, 4096, seqs, G) == D
         assert _order(1, chunk, 256, 4096, seqs, G) == S
