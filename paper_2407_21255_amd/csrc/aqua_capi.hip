@@ -640,7 +640,9 @@ aqua::SwapLaunch make_launch(aqua_kv_pool* p, bool is_in, uint8_t* img, const Ru
 //
 // The copies moving sequence q's layers [l0, l0 + nl) between a slot and the
 // host image: one piece when the image holds exactly the table's blocks,
-// else one per layer (only the first n of its m blocks).
+// else one per layer (only the first n of its m blocks).  Pieces that continue
+// each other on both sides become one copy: packed images of a call that is
+// one layer group, whose slot then has the images' own layout.
 void stage_pieces(aqua_kv_pool* p, bool to_host, const void* buf, uint8_t* slot, uint32_t G,
                   uint32_t l0, uint32_t nl, std::vector<aqua::LinkPiece>* out) {
     const uint64_t C = p->shape.C;
@@ -654,8 +656,8 @@ void stage_pieces(aqua_kv_pool* p, bool to_host, const void* buf, uint8_t* slot,
             const uint64_t l = l0 + j;
             uint8_t* hj = h + l * q.m * C;
             uint8_t* sj = s + (uint64_t)j * q.n * C;
-            out->push_back(to_host ? aqua::LinkPiece{hj, sj, bytes}
-                                   : aqua::LinkPiece{sj, hj, bytes});
+            aqua::append_piece(out, to_host ? aqua::LinkPiece{hj, sj, bytes}
+                                            : aqua::LinkPiece{sj, hj, bytes});
         }
     }
 }
@@ -1184,7 +1186,8 @@ aqua_status do_migrate(aqua_kv_pool* p, const void* src, uint64_t src_bytes, int
         std::vector<aqua::LinkPiece> copies;
         for (uint32_t k = 0; k < n; ++k)
             if (len[k])
-                copies.push_back({(uint8_t*)dst + dof[k], (const uint8_t*)src + so[k], len[k]});
+                aqua::append_piece(&copies, {(uint8_t*)dst + dof[k], (const uint8_t*)src + so[k],
+                                             len[k]});
         aqua::LinkEngine& w = p->link[link_dir];
         int64_t* flag = nullptr;
         const uint64_t job = w.submit(copies, &flag);

@@ -310,6 +310,17 @@ size_t plan_copies(uint32_t n, const uint64_t* src_off, const uint64_t* dst_off,
     return out->size() - before;
 }
 
+void append_piece(std::vector<LinkPiece>* v, const LinkPiece& p) {
+    if (!v->empty()) {
+        LinkPiece& q = v->back();
+        if ((char*)q.dst + q.bytes == p.dst && (const char*)q.src + q.bytes == p.src) {
+            q.bytes += p.bytes;
+            return;
+        }
+    }
+    v->push_back(p);
+}
+
 uint64_t pack_ranges(uint32_t n, const uint64_t* src_off, const uint64_t* dst_off,
                      const uint64_t* len, InlineRanges* out, uint32_t* count) {
     uint64_t pieces = 0;

@@ -108,6 +108,17 @@ constexpr CopyDesc piece_of(const InlineRanges& r, uint32_t count, uint64_t u) {
 size_t plan_copies(uint32_t n, const uint64_t* src_off, const uint64_t* dst_off,
                    const uint64_t* len, uint64_t unit, std::vector<CopyDesc>* out);
 
+// One copy over the host link.
+struct LinkPiece {
+    void* dst;
+    const void* src;
+    uint64_t bytes;
+};
+// Appends a copy, as part of the last one where it continues that on both
+// sides: a copy engine spends about 20 us on each copy beyond its bytes, so 36
+// sequences of 1.2 MiB took 1.2 ms more than one copy of them all.
+void append_piece(std::vector<LinkPiece>* v, const LinkPiece& p);
+
 // Work item of the copy kernels: a run of `nchunks` consecutive pool blocks
 // starting at `block` whose image chunks are also consecutive.  In layer l
 // the pool side starts at (l*N + block)*C and the image side at

@@ -145,6 +145,21 @@ uint32_t aqua_core_xcd_window_unit(uint32_t block, uint32_t units) {
     return aqua::xcd_window_unit(block, units);
 }
 
+// Appends n (dst, src, bytes) copies one by one; writes the resulting list and
+// returns its length.
+uint64_t aqua_core_append_pieces(const uint64_t* in, uint64_t n, uint64_t* out) {
+    std::vector<aqua::LinkPiece> v;
+    for (uint64_t k = 0; k < n; ++k)
+        aqua::append_piece(&v, {(void*)(uintptr_t)in[3 * k],
+                                (const void*)(uintptr_t)in[3 * k + 1], in[3 * k + 2]});
+    for (size_t k = 0; k < v.size(); ++k) {
+        out[3 * k] = (uint64_t)(uintptr_t)v[k].dst;
+        out[3 * k + 1] = (uint64_t)(uintptr_t)v[k].src;
+        out[3 * k + 2] = v[k].bytes;
+    }
+    return v.size();
+}
+
 uint32_t aqua_core_run_threads(uint64_t run_bytes, int32_t capped) {
     return aqua::run_threads(run_bytes, capped != 0);
 }

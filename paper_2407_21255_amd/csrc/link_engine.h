@@ -45,6 +45,8 @@
 #include <thread>
 #include <vector>
 
+#include "aqua_core.h"
+
 namespace aqua {
 
 // The GPU agent of a HIP device and the CPU agent nearest to it.
@@ -69,12 +71,6 @@ void link_auto_engines(const LinkAgents& a, int32_t* d2h, int32_t* h2d);
 // each non-null flag (a job's ready flag from LinkEngine::submit): the
 // stores are ordered after everything enqueued on `stream` before it.
 hipError_t launch_release_flags(int64_t* a, int64_t* b, hipStream_t stream);
-
-struct LinkPiece {
-    void* dst;
-    const void* src;
-    uint64_t bytes;
-};
 
 class LinkEngine {
   public:

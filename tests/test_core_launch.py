@@ -129,3 +129,23 @@ def test_copy_windows_are_a_bijection(units):
     for base in range(0, units - 63, 64):
         for x in range(8):
             assert got[base + x:base + 64:8] == list(range(base + 8 * x, base + 8 * x + 8))
+
+
+def test_link_copies_merge_only_where_both_sides_continue():
+    fn = core_lib.lib().aqua_core_append_pieces
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_uint64, ctypes.c_void_p]
+    fn.restype = ctypes.c_uint64
+
+    def merged(pieces):
+        a = np.array(pieces, dtype=np.uint64).reshape(-1, 3)
+        out = np.zeros_like(a)
+        n = fn(a.ctypes.data, len(a), out.ctypes.data)
+        return [tuple(int(x) for x in r) for r in out[:n]]
+
+    assert merged([]) == []
+    assert merged([(100, 900, 10), (110, 910, 20), (130, 930, 5)]) == [(100, 900, 35)]
+    for apart in ([(100, 900, 10), (110, 911, 20)], [(100, 900, 10), (111, 910, 20)],
+                  [(100, 900, 10), (90, 890, 10)], [(100, 900, 10), (100, 900, 10)]):
+        assert merged(apart) == apart
+    assert merged([(0x100, 0x900, 16), (0x110, 0x910, 16), (0x130, 0x920, 16),
+                   (0x140, 0x930, 16)]) == [(0x100, 0x900, 32), (0x130, 0x920, 32)]
