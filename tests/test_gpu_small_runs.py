@@ -199,3 +199,13 @@ def test_range_copies_of_few_and_many_ranges(n, where):
     finally:
         kv.close()
     assert_bytes_equal(host(dst), want, "destination and gaps")
+
+
+def test_default_stream_is_the_current_one():
+    """No stream given: the caller's current stream, inside and outside a
+    stream context (None stands for the null stream)."""
+    assert aqua._stream_handle(None) == (torch.cuda.current_stream().cuda_stream or None)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        assert aqua._stream_handle(None) == s.cuda_stream
+    assert aqua._stream_handle(None) == aqua._stream_handle(torch.cuda.current_stream())
