@@ -190,9 +190,20 @@ uint32_t swap_threads(uint64_t chunk_bytes, uint32_t min_threads) {
     return t;
 }
 
-uint32_t run_threads(uint64_t run_bytes, bool capped) {
-    if (capped || run_bytes >= kFullWorkgroupRun) return kMaxThreads;
-    return std::min<uint32_t>(kMaxThreads / 2, swap_threads(run_bytes * kUnroll, 64));
+PartGrid part_grid(uint32_t units, uint64_t mean_run_bytes, uint64_t max_run_bytes) {
+    const uint64_t slots = units < kSpreadUnits ? units : ((uint64_t)units + 7) / 8 * 8;
+    auto pieces = [](uint64_t bytes) {
+        return std::max<uint64_t>(1, bytes / kPartBytes + (bytes % kPartBytes != 0));
+    };
+    // 16384 waves fill the chip twice.
+    uint64_t parts = pieces(max_run_bytes);
+    if (slots * parts > 16384) parts = std::min(parts, pieces(mean_run_bytes));
+    while (parts > 1 && slots * parts > kMaxPartGrid) parts = (parts + 1) / 2;
+    PartGrid g;
+    g.parts = (uint32_t)parts;
+    g.total = (uint32_t)(slots * parts);
+    g.grid = std::min(g.total, kMaxPartGrid);
+    return g;
 }
 
 RunOrder run_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t num_blocks,

@@ -163,26 +163,60 @@ constexpr RunDesc unpack_inline(const InlineRun& r) {
 // vectors per pass, so a workgroup of `threads` lanes has threads * 64 bytes
 // in flight.  swap_threads sizes a workgroup so that every lane issues kUnroll
 // loads before its first store: 1024 lanes for 64 KiB and more, fewer for
-// less (down to min_threads, a power of two of at least 64).
+// less (down to min_threads, a power of two of at least 64).  Launches of a
+// capped grid, whose workgroups loop over units, ask for the full 1024: there a
+// workgroup's lanes are what is in flight.
 constexpr uint32_t kUnroll = 4;
 constexpr uint32_t kMaxThreads = 1024;
 uint32_t swap_threads(uint64_t chunk_bytes, uint32_t min_threads);
 
-// Lanes of a swap launch whose runs average `run_bytes`: 1024 from 16 KiB up,
-// below that one 16-byte vector per lane (a power of two of at least 64 and
-// at most 512 lanes).  What bounds short runs is the rate at which waves
-// start: a 1024-lane workgroup is 16 waves, and with 8 KiB runs half of them,
-// with 2 KiB runs 14 of 16, have nothing to copy.  Measured on MI355X, HBM
-// traffic of the gather at about 1.2 GiB per call, 1024 lanes against this
-// rule: 8 KiB runs 4.9 -> 6.1 TB/s, 4 KiB 3.0 -> 6.0, 2 KiB 1.6 -> 5.5;
-// scatters the same.  Two or four vectors per lane (fewer waves still) were
-// 1-7 % slower than one; 16 KiB runs took 1-5 % longer with 512 or 256 lanes
-// than with 1024, 10 to 12 KiB runs 4-6 % less with 512 than with 1024.
-// `capped` launches (a limited grid that loops over its units, such as the
-// zero-copy host path's 16 workgroups) keep 1024: there a workgroup's lanes
-// are what is in flight.
-constexpr uint64_t kFullWorkgroupRun = 16ull << 10;
-uint32_t run_threads(uint64_t run_bytes, bool capped);
+// How an uncapped swap launch splits its units: each unit, one (layer, run), is
+// cut into `parts` of about 1 KiB, each the work of a workgroup of one wave, one
+// 16-byte vector per lane.  A wave ends, and its slot is refilled, as soon as
+// its 1 KiB is stored; a 1024-lane workgroup holds the slots of its 16 waves
+// until the last of its 64 KiB, and runs that are no multiple of 16 KiB leave
+// some of them idle.  Measured on MI355X against one 1024-lane workgroup per unit
+// (HBM traffic, 32 MiB to 5 GiB per call): 64 KiB chunks 5.95 -> 6.3 TB/s, 4 to
+// 12 % at every size; 128 KiB 10 to 19 %; 32 KiB 1 to 10 %; 16 KiB 0 to 7 %; 8 KiB
+// 4.9 -> 6.1 TB/s; 2 KiB 1.6 -> 5.5; one 1 MiB chunk in 32 layers 42 -> 14 us.  4 KiB
+// parts of 256 lanes were as good from 512 MiB on, 8 KiB of 512 lanes 1-2 % behind,
+// more vectors per lane 2-7 %.
+// The parts of a unit go to the XCD the whole unit would go to (part_at), so
+// that dealt runs stay dealt; below kSpreadUnits units they go to all XCDs.
+constexpr uint64_t kPartBytes = 1ull << 10;
+constexpr uint32_t kPartThreads = 64;
+constexpr uint32_t kSpreadUnits = 64;
+// A dispatch counts its work-items in 32 bits: 2^25 workgroups of 64 lanes.
+constexpr uint32_t kMaxPartGrid = 1u << 25;
+struct PartGrid {
+    uint32_t parts;  // per unit
+    uint32_t total;  // indices for part_at: parts times the units, padded
+    uint32_t grid;   // workgroups: total, at most kMaxPartGrid
+};
+// Runs of one length have as many parts as 1 KiB pieces.  Where lengths differ,
+// the mean decides for large calls (workgroups past a short run's end return,
+// and those of a long run copy more than 1 KiB) and the longest for small ones.
+PartGrid part_grid(uint32_t units, uint64_t mean_run_bytes, uint64_t max_run_bytes);
+struct UnitPart {
+    uint32_t unit, part;  // unit >= units: padding, nothing to do
+};
+// Index b of a launch's total: a bijection onto (unit, part), and padding.
+constexpr UnitPart part_at(uint32_t b, uint32_t units, uint32_t parts) {
+    if (units < kSpreadUnits) return UnitPart{b / parts, b % parts};
+    const uint32_t j = b / 8;
+    return UnitPart{j / parts * 8 + b % 8, j % parts};
+}
+// 16-byte vectors [lo, lo + n) of a run's nvec that part `part` copies.
+struct VecRange {
+    uint32_t lo, n;
+};
+constexpr VecRange part_range(uint32_t nvec, uint32_t parts, uint32_t part) {
+    const uint32_t even = nvec / parts + (nvec % parts != 0);
+    const uint32_t per = (even + kPartThreads - 1) / kPartThreads * kPartThreads;
+    const uint64_t lo = (uint64_t)part * per;
+    if (lo >= nvec) return VecRange{nvec, 0};
+    return VecRange{(uint32_t)lo, nvec - (uint32_t)lo < per ? nvec - (uint32_t)lo : per};
+}
 
 // Workgroups of one launch over `units` work units: one per unit, at most
 // `max_workgroups` when that is non-zero, and never more than kMaxGrid.  A
@@ -227,7 +261,7 @@ RunOrder run_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t n
                    uint32_t num_seqs);
 
 // run_order refined by the bytes a call of chunks under 64 KiB moves, for the
-// calls that run_order leaves in table order.  With the lanes of run_threads
+// calls that run_order leaves in table order.  With workgroups sized to the runs
 // and nontemporal stores (nt_pool_store), dealing pays there too.  Measured on
 // MI355X, 32 layers, one and 16 sequences, a third and an eighth of the pool,
 // cold caches, against table order (and, between 16 and 64 KiB, the XCD unit

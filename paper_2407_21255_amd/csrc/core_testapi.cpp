@@ -160,8 +160,24 @@ uint64_t aqua_core_append_pieces(const uint64_t* in, uint64_t n, uint64_t* out) 
     return v.size();
 }
 
-uint32_t aqua_core_run_threads(uint64_t run_bytes, int32_t capped) {
-    return aqua::run_threads(run_bytes, capped != 0);
+void aqua_core_part_grid(uint32_t units, uint64_t mean_bytes, uint64_t max_bytes, uint32_t* out) {
+    const aqua::PartGrid g = aqua::part_grid(units, mean_bytes, max_bytes);
+    out[0] = g.parts;
+    out[1] = g.total;
+    out[2] = g.grid;
+}
+
+// Copies bytes as the part kernels would, index by index: adds 1 to
+// hits[u * nvec[k] ...] for each vector that part_at and part_range give to unit
+// u of run k = u % ndesc.  base[u] is the unit's first entry.
+void aqua_core_part_hits(uint32_t total, uint32_t units, uint32_t parts, uint32_t ndesc,
+                         const uint32_t* nvec, const uint64_t* base, uint8_t* hits) {
+    for (uint32_t b = 0; b < total; ++b) {
+        const aqua::UnitPart q = aqua::part_at(b, units, parts);
+        if (q.unit >= units) continue;
+        const aqua::VecRange r = aqua::part_range(nvec[q.unit % ndesc], parts, q.part);
+        for (uint32_t i = 0; i < r.n; ++i) ++hits[base[q.unit] + r.lo + i];
+    }
 }
 
 void* aqua_core_tracker_new(uint32_t num_blocks) {

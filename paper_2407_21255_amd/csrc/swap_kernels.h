@@ -21,10 +21,11 @@ struct SwapLaunch {
     uint32_t num_layers;
     uint64_t chunk_bytes;     // C
     uint64_t pool_lstride;    // N * C
-    uint32_t max_workgroups;  // 0: one workgroup per (layer, run)
+    uint64_t mean_run_bytes;  // per layer
+    uint64_t max_run_bytes;
+    uint32_t max_workgroups;  // 0: as many as part_grid says
     bool nt_pool_store;       // scatter: nontemporal stores into the pool
-    uint32_t threads;         // lanes per workgroup: 64, 128, 256, 512 or 1024
-    bool xcd_order;           // one-pass launches: each XCD takes a contiguous eighth of units
+    bool xcd_order;           // uncapped launches: each XCD takes a contiguous eighth of units
 };
 
 // Scatter store hint, measured on MI355X.  Nontemporal pool stores pay for

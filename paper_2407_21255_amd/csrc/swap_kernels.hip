@@ -1,21 +1,19 @@
 // swap_kernels.hip -- gfx950 gather (swap-out) and scatter (swap-in) kernels.
 //
 // The work is pure data movement (Aqua, section 7, "Efficient context
-// switching"): no arithmetic on the values, so no MFMA and no LDS.  Each
-// workgroup copies one run of chunks of one layer at a time; every lane
-// moves 16-byte vectors, a wave covers 1 KiB contiguous per instruction,
-// and kUnroll = 4 independent loads are issued before the first store, so a
-// workgroup of 1024 lanes (16 wave64s) holds one 64 KiB bf16 chunk in flight.
-// The kernels also come in 512, 256, 128 and 64 lanes: runs under 16 KiB are
-// bound by the rate at which waves start, so a launch takes no more waves
-// than its runs fill (run_threads).
+// switching"): no arithmetic on the values, so no MFMA and no LDS.  What bounds
+// it is HBM, its write side above all, and for short runs the rate at which
+// waves start.  A unit of work is one run of chunks in one layer; it is cut into
+// parts of about 1 KiB, each copied by a workgroup of one wave with one 16-byte
+// vector per lane, and the parts of a unit stay on one XCD (part_grid).
+// Launches of a capped grid (zero-copy host swaps) use 1024-lane workgroups
+// that loop over whole units with kUnroll = 4 loads per lane in flight.
 // The run descriptor is uniform across the workgroup and is fetched with
-// scalar loads.  The offload side is written (swap-out) or read (swap-in) with
+// scalar loads.  Cache hints: the offload side is written (swap-out) or read (swap-in) with
 // nontemporal hints: it is touched once and should not displace the pool's
 // working set in L2 and MALL.  The gather's pool loads are nontemporal too;
-// the scatter's pool stores are nontemporal for chunks of 64 KiB and more
-// and for calls that write 2 GiB or more, where that measured faster, and
-// ordinary otherwise (nt_pool_store).
+// the scatter's pool stores are nontemporal or ordinary by chunk size, bytes
+// and run order (nt_pool_store).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -105,60 +103,104 @@ __device__ __forceinline__ void copy_span(const v4u* __restrict__ s,
 // plain order consecutive workgroups take consecutive units; with xcd_order
 // each XCD takes a contiguous eighth of them (xcd_unit), and the host may
 // have dealt each layer's runs out to the XCDs already (interleave_runs).
-// `runs` holds the descriptors: a device-accessible array, or the kernel's own
-// argument (InlineRuns).  Either way they are uniform across the workgroup.
-struct RingRuns {
-    const RunDesc* __restrict__ descs;
-    __device__ __forceinline__ RunDesc operator()(uint32_t k) const { return descs[k]; }
-};
+// One unit: vectors [r.lo, r.lo + r.n) of run dsc in layer l.
+template <bool OUT, bool NT_POOL_ST, int THREADS>
+__device__ __forceinline__ void swap_unit(uint8_t* __restrict__ pool, uint8_t* __restrict__ img,
+                                          const RunDesc& dsc, uint32_t l, uint32_t img_l0,
+                                          VecRange r, uint64_t chunk_bytes,
+                                          uint64_t pool_lstride) {
+    uint8_t* p = pool + (uint64_t)l * pool_lstride + (uint64_t)dsc.block * chunk_bytes;
+    uint8_t* m = img + dsc.img_off + (uint64_t)(l - img_l0) * dsc.img_lstride;
+    if constexpr (OUT)
+        copy_span<THREADS, AQUA_NT_OUT_LD, AQUA_NT_OUT_ST>(
+            reinterpret_cast<const v4u*>(p) + r.lo, reinterpret_cast<v4u*>(m) + r.lo, r.n);
+    else
+        copy_span<THREADS, AQUA_NT_IN_LD, NT_POOL_ST>(
+            reinterpret_cast<const v4u*>(m) + r.lo, reinterpret_cast<v4u*>(p) + r.lo, r.n);
+}
 
-template <bool OUT, bool NT_POOL_ST, int THREADS, typename Get>
-__device__ __forceinline__ void swap_units(
+__device__ __forceinline__ uint32_t run_vectors(const RunDesc& dsc, uint64_t chunk_bytes) {
+    return (uint32_t)((uint64_t)dsc.nchunks * chunk_bytes / 16);
+}
+
+// Uncapped launches: a wave per part of a unit (part_grid says why).  The loop
+// ends after one pass unless the launch has more parts than a dispatch counts.
+template <bool OUT, bool NT_POOL_ST, typename Get>
+__device__ __forceinline__ void swap_parts(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const Get& get, uint32_t ndesc,
-    uint32_t l0, uint32_t img_l0, uint32_t units, uint64_t chunk_bytes, uint64_t pool_lstride,
-    uint32_t xcd_order) {
-    // With one workgroup per unit, xcd_order gives each XCD (workgroups go
-    // to the 8 XCDs in turn) a contiguous eighth of the units.
-    const uint32_t u0 =
-        (xcd_order && gridDim.x == units) ? xcd_unit(blockIdx.x, units) : blockIdx.x;
-    for (uint32_t u = u0; u < units; u += gridDim.x) {
-        const uint32_t l = l0 + u / ndesc;
-        const uint32_t k = u - (u / ndesc) * ndesc;
-        const RunDesc dsc = get(k);
-        uint8_t* p = pool + (uint64_t)l * pool_lstride + (uint64_t)dsc.block * chunk_bytes;
-        uint8_t* m = img + dsc.img_off + (uint64_t)(l - img_l0) * dsc.img_lstride;
-        const uint32_t nvec = (uint32_t)((uint64_t)dsc.nchunks * chunk_bytes / 16);
-        if constexpr (OUT)
-            copy_span<THREADS, AQUA_NT_OUT_LD, AQUA_NT_OUT_ST>(
-                reinterpret_cast<const v4u*>(p), reinterpret_cast<v4u*>(m), nvec);
-        else
-            copy_span<THREADS, AQUA_NT_IN_LD, NT_POOL_ST>(
-                reinterpret_cast<const v4u*>(m), reinterpret_cast<v4u*>(p), nvec);
+    uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
+    uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
+    for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {
+        const UnitPart q = part_at(b, units, parts);
+        if (q.unit >= units) continue;
+        const uint32_t u = xcd_order ? xcd_unit(q.unit, units) : q.unit;
+        const uint32_t l = u / ndesc;
+        const RunDesc dsc = get(u - l * ndesc);
+        const VecRange r = part_range(run_vectors(dsc, chunk_bytes), parts, q.part);
+        swap_unit<OUT, NT_POOL_ST, kPartThreads>(pool, img, dsc, l0 + l, img_l0, r, chunk_bytes,
+                                                 pool_lstride);
     }
 }
 
-template <bool OUT, bool NT_POOL_ST, int THREADS>
-__global__ __launch_bounds__(THREADS) void swap_runs_kernel(
-    uint8_t* __restrict__ pool, uint8_t* __restrict__ img,
-    const RunDesc* __restrict__ descs, uint32_t ndesc, uint32_t l0, uint32_t img_l0,
-    uint32_t units, uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
-    swap_units<OUT, NT_POOL_ST, THREADS>(pool, img, RingRuns{descs}, ndesc, l0, img_l0, units,
-                                         chunk_bytes, pool_lstride, xcd_order);
+// Capped launches: 1024-lane workgroups that loop over whole units.
+template <bool OUT, bool NT_POOL_ST, typename Get>
+__device__ __forceinline__ void swap_units(
+    uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const Get& get, uint32_t ndesc,
+    uint32_t l0, uint32_t img_l0, uint32_t units, uint64_t chunk_bytes, uint64_t pool_lstride) {
+    for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
+        const uint32_t l = u / ndesc;
+        const RunDesc dsc = get(u - l * ndesc);
+        swap_unit<OUT, NT_POOL_ST, kMaxThreads>(pool, img, dsc, l0 + l, img_l0,
+                                                VecRange{0, run_vectors(dsc, chunk_bytes)},
+                                                chunk_bytes, pool_lstride);
+    }
 }
 
-// The same with the runs in the kernel's arguments, for calls of at most
-// kInlineRuns runs: a workgroup's descriptor comes from the argument segment
-// instead of over the host link, and the call needs no ring space, no upload
-// kernel and no device scratch.  A 32 MiB allocation-free round trip went from
-// four launches and 42 us to two and 34 us.
-template <bool OUT, bool NT_POOL_ST, int THREADS, uint32_t CAP>
-__global__ __launch_bounds__(THREADS) void swap_runs_inline_kernel(
+// Each in two forms.  Runs in device-accessible memory (the pinned ring, the
+// device ring or the scratch):
+template <bool OUT, bool NT_POOL_ST>
+__global__ __launch_bounds__(kPartThreads) void swap_runs_kernel(
+    uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const RunDesc* __restrict__ descs,
+    uint32_t ndesc, uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
+    uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
+    swap_parts<OUT, NT_POOL_ST>(
+        pool, img, [&](uint32_t k) { return descs[k]; }, ndesc, l0, img_l0, units, parts, total,
+        chunk_bytes, pool_lstride, xcd_order);
+}
+
+template <bool OUT, bool NT_POOL_ST>
+__global__ __launch_bounds__(kMaxThreads) void swap_runs_capped_kernel(
+    uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const RunDesc* __restrict__ descs,
+    uint32_t ndesc, uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
+    uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
+    swap_units<OUT, NT_POOL_ST>(
+        pool, img, [&](uint32_t k) { return descs[k]; }, ndesc, l0, img_l0, units, chunk_bytes,
+        pool_lstride);
+}
+
+// and runs in the kernel's arguments, for calls of at most kInlineRuns runs: a
+// workgroup's descriptor comes from the argument segment instead of over the
+// host link, and the call needs no ring space, no upload kernel and no device
+// scratch.  A 32 MiB allocation-free round trip went from four launches and
+// 42 us to two and 34 us.
+template <bool OUT, bool NT_POOL_ST, uint32_t CAP>
+__global__ __launch_bounds__(kPartThreads) void swap_runs_inline_kernel(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const InlineArg<CAP> runs,
-    uint32_t ndesc, uint32_t l0, uint32_t img_l0, uint32_t units, uint64_t chunk_bytes, uint64_t pool_lstride,
-    uint32_t xcd_order) {
-    swap_units<OUT, NT_POOL_ST, THREADS>(
+    uint32_t ndesc, uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
+    uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
+    swap_parts<OUT, NT_POOL_ST>(
         pool, img, [&](uint32_t k) { return unpack_inline(runs.run[k]); }, ndesc, l0, img_l0,
-        units, chunk_bytes, pool_lstride, xcd_order);
+        units, parts, total, chunk_bytes, pool_lstride, xcd_order);
+}
+
+template <bool OUT, bool NT_POOL_ST>
+__global__ __launch_bounds__(kMaxThreads) void swap_runs_inline_capped_kernel(
+    uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const InlineRuns runs, uint32_t ndesc,
+    uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
+    uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
+    swap_units<OUT, NT_POOL_ST>(
+        pool, img, [&](uint32_t k) { return unpack_inline(runs.run[k]); }, ndesc, l0, img_l0,
+        units, chunk_bytes, pool_lstride);
 }
 
 // Range copy between two offload buffers (image migration): work unit u
@@ -243,33 +285,31 @@ hipError_t launch_with_event(const void* fn, uint32_t grid, uint32_t threads, vo
     return e == hipSuccess ? hipEventRecord(done, stream) : e;
 }
 
-template <bool OUT, bool NT_POOL_ST, int THREADS>
-hipError_t launch_swap_k(const SwapLaunch& a, uint32_t grid, uint32_t l0, uint32_t units,
-                         hipStream_t stream, hipEvent_t done) {
+template <bool OUT, bool NT_POOL_ST>
+hipError_t launch_swap_k(const SwapLaunch& a, uint32_t l0, uint32_t units, hipStream_t stream,
+                         hipEvent_t done) {
+    const bool capped = a.max_workgroups != 0;
+    const PartGrid g = part_grid(units, a.mean_run_bytes, a.max_run_bytes);
+    const uint32_t grid = capped ? launch_grid(units, a.max_workgroups) : g.grid;
+    const uint32_t threads = capped ? swap_threads(a.chunk_bytes, kMaxThreads) : kPartThreads;
     // The argument array hands the runtime the runs where they are; passed by
     // value they would be copied once more.  The shorter argument is a prefix
     // of the longer one.
     const uint32_t xcd = a.xcd_order;
     const void* runs = a.inl ? (const void*)a.inl : (const void*)&a.descs;
-    const void* args[] = {&a.pool, &a.img, runs, &a.ndesc, &l0, &a.img_l0, &units,
-                          &a.chunk_bytes, &a.pool_lstride, &xcd};
-    const void* fn = reinterpret_cast<const void*>(&swap_runs_kernel<OUT, NT_POOL_ST, THREADS>);
-    if (a.inl && a.ndesc <= kInlineFew)
-        fn = reinterpret_cast<const void*>(
-            &swap_runs_inline_kernel<OUT, NT_POOL_ST, THREADS, kInlineFew>);
-    else if (a.inl)
-        fn = reinterpret_cast<const void*>(
-            &swap_runs_inline_kernel<OUT, NT_POOL_ST, THREADS, kInlineRuns>);
-    return launch_with_event(fn, grid, THREADS, const_cast<void**>(args), stream, done);
-}
-
-template <int THREADS>
-hipError_t launch_swap_t(const SwapLaunch& a, uint32_t grid, uint32_t l0, uint32_t units,
-                         hipStream_t stream, hipEvent_t done) {
-    if (a.out) return launch_swap_k<true, false, THREADS>(a, grid, l0, units, stream, done);
-    if (a.nt_pool_store)
-        return launch_swap_k<false, true, THREADS>(a, grid, l0, units, stream, done);
-    return launch_swap_k<false, false, THREADS>(a, grid, l0, units, stream, done);
+    const void* args[] = {&a.pool, &a.img,   runs,     &a.ndesc,       &l0,             &a.img_l0,
+                          &units,  &g.parts, &g.total, &a.chunk_bytes, &a.pool_lstride, &xcd};
+    const void* fn;
+    if (!a.inl)
+        fn = capped ? reinterpret_cast<const void*>(&swap_runs_capped_kernel<OUT, NT_POOL_ST>)
+                    : reinterpret_cast<const void*>(&swap_runs_kernel<OUT, NT_POOL_ST>);
+    else if (capped)
+        fn = reinterpret_cast<const void*>(&swap_runs_inline_capped_kernel<OUT, NT_POOL_ST>);
+    else if (a.ndesc <= kInlineFew)
+        fn = reinterpret_cast<const void*>(&swap_runs_inline_kernel<OUT, NT_POOL_ST, kInlineFew>);
+    else
+        fn = reinterpret_cast<const void*>(&swap_runs_inline_kernel<OUT, NT_POOL_ST, kInlineRuns>);
+    return launch_with_event(fn, grid, threads, const_cast<void**>(args), stream, done);
 }
 
 }  // namespace
@@ -294,17 +334,11 @@ hipError_t launch_swap(const SwapLaunch& a, hipStream_t stream, uint64_t* launch
     for (uint32_t l0 = a.first_layer; l0 < end; l0 += per) {
         const uint32_t nl = std::min<uint32_t>(per, end - l0);
         const uint32_t units = nl * a.ndesc;
-        const uint32_t grid = launch_grid(units, a.max_workgroups);
         const hipEvent_t last = l0 + nl == end ? done : nullptr;
-        hipError_t e = hipErrorInvalidValue;
-        switch (a.threads) {
-            case 1024: e = launch_swap_t<1024>(a, grid, l0, units, stream, last); break;
-            case 512: e = launch_swap_t<512>(a, grid, l0, units, stream, last); break;
-            case 256: e = launch_swap_t<256>(a, grid, l0, units, stream, last); break;
-            case 128: e = launch_swap_t<128>(a, grid, l0, units, stream, last); break;
-            case 64: e = launch_swap_t<64>(a, grid, l0, units, stream, last); break;
-            default: break;
-        }
+        const hipError_t e = a.out ? launch_swap_k<true, false>(a, l0, units, stream, last)
+                             : a.nt_pool_store
+                                 ? launch_swap_k<false, true>(a, l0, units, stream, last)
+                                 : launch_swap_k<false, false>(a, l0, units, stream, last);
         if (e != hipSuccess) return e;
         if (launches) ++*launches;
     }

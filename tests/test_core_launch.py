@@ -9,17 +9,50 @@ from tests import core_lib
 K = 1 << 10
 
 
-@pytest.mark.parametrize("run_bytes,lanes", [
-    (16, 64), (1008, 64), (1024, 64), (1040, 128), (2 * K, 128), (2 * K + 16, 256), (4 * K, 256),
-    (4 * K + 16, 512), (6 * K, 512), (8 * K, 512), (10 * K, 512), (16 * K - 16, 512),
-    (16 * K, 1024), (40 * K, 1024), (64 * K, 1024), (1 << 30, 1024), (0, 64)])
-def test_lanes_follow_the_mean_run(run_bytes, lanes):
-    """One vector per lane below 16 KiB, 1024 lanes from there up; capped
-    grids always 1024."""
-    fn = core_lib.lib().aqua_core_run_threads
-    fn.argtypes, fn.restype = [ctypes.c_uint64, ctypes.c_int32], ctypes.c_uint32
-    assert fn(run_bytes, 0) == lanes
-    assert fn(run_bytes, 1) == 1024
+def _part_grid(units, mean, longest):
+    fn = core_lib.lib().aqua_core_part_grid
+    fn.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_void_p]
+    fn.restype = None
+    out = np.zeros(3, dtype=np.uint32)
+    fn(units, mean, longest, out.ctypes.data)
+    return tuple(int(x) for x in out)     # parts, total, grid
+
+
+@pytest.mark.parametrize("units,mean,longest,want", [
+    (1, 16, 16, (1, 1, 1)), (63, 1024, 1024, (1, 63, 63)), (64, 1024, 1024, (1, 64, 64)),
+    (65, 1025, 1025, (2, 144, 144)), (128, 64 * K, 64 * K, (64, 8192, 8192)),
+    (163840, 64 * K, 64 * K, (64, 10485760, 10485760)),
+    # Runs of several lengths: the longest decides for few waves, the mean for many.
+    (8, 3 * K, 64 * K, (64, 512, 512)), (32768, 3 * K, 64 * K, (3, 98304, 98304)),
+    # More parts than a dispatch counts: fewer, then a loop.
+    (1 << 20, 64 * K, 64 * K, (32, 1 << 25, 1 << 25)),
+    (1 << 25, 2 * K, 2 * K, (1, 1 << 25, 1 << 25)),
+    ((1 << 31) - 1, 32, 32, (1, 1 << 31, 1 << 25)), (4, 1 << 30, 1 << 30, (1 << 20, 1 << 22, 1 << 22))])
+def test_a_wave_per_kib_of_a_run(units, mean, longest, want):
+    parts, total, grid = got = _part_grid(units, mean, longest)
+    assert got == want
+    assert grid * 64 < 1 << 32 and total >= units and total % parts == 0
+
+
+@pytest.mark.parametrize("units", [1, 2, 7, 63, 64, 65, 71, 72, 130])
+@pytest.mark.parametrize("lengths", [(1,), (64,), (65,), (4096,), (1, 64, 65, 700, 4096), (640, 641)])
+def test_parts_cover_every_vector_once(units, lengths):
+    """Over the whole index range of a launch every vector of every unit is
+    copied exactly once, for one run length and for several, with as many
+    parts as the rule gives, fewer and more."""
+    fn = core_lib.lib().aqua_core_part_hits
+    P = ctypes.c_void_p
+    fn.argtypes, fn.restype = [ctypes.c_uint32] * 4 + [P, P, P], None
+    nvec = np.array(lengths, dtype=np.uint32)
+    n = len(nvec)
+    per_unit = nvec[np.arange(units) % n].astype(np.uint64)
+    base = np.concatenate([[0], np.cumsum(per_unit)]).astype(np.uint64)
+    parts0, _, _ = _part_grid(units, int(nvec.mean() * 16), int(nvec.max()) * 16)
+    slots = units if units < 64 else -(-units // 8) * 8
+    for parts in sorted({1, 2, 3, parts0, parts0 + 1}):
+        hits = np.zeros(int(base[-1]), dtype=np.uint8)
+        fn(slots * parts, units, parts, n, nvec.ctypes.data, base.ctypes.data, hits.ctypes.data)
+        assert (hits == 1).all(), parts
 
 
 def _order(is_in, chunk, blocks, num_blocks, seqs, nbytes):
