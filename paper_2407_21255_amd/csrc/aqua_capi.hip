@@ -35,7 +35,9 @@ constexpr uint32_t kHostZeroCopyWorkgroups = 16;
 // finished launches where it meets such a packet.  Without any, 20000 calls
 // issued with no sync left 12 ms of that work behind, which slowed the
 // process's next HIP calls (a 1 us allocation took 5 us); with one in 32 none
-// was left, at 0.1-0.2 us per call.
+// was left, at 0.1-0.2 us per call.  Calls whose kernel writes or reads host
+// memory always record it: a record releases to the host also what a pinned
+// buffer that isn't coherent may hold back, and 2.5 us are nothing on the link.
 constexpr uint64_t kRecordEvery = 32;
 
 // Measurement switches: the defaults are the shipped configuration, the
@@ -1048,7 +1050,7 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
                 make_launch(p, is_in, dbuf, reinterpret_cast<const RunDesc*>(descs),
                             (uint32_t)p->plan.size(), target, l_begin, l_count);
             L.xcd_order = target == AQUA_TARGET_DEVICE && aqua::xcd_unit_order(p->shape.C, dealt);
-            recorded = ticket % kRecordEvery != 0;
+            recorded = !zero_copy && ticket % kRecordEvery != 0;
             if (recorded && !rec.ev) e = take_event(p, &rec.ev);
             if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
             (void)hipGetLastError();
@@ -1212,9 +1214,9 @@ aqua_status do_migrate(aqua_kv_pool* p, const void* src, uint64_t src_bytes, int
     }
     hipError_t e = take_event(p, &rec.ev);
     if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
-    const bool recorded = L.pieces && ticket % kRecordEvery != 0;
+    const bool host_side = src_target == AQUA_TARGET_HOST || dst_target == AQUA_TARGET_HOST;
+    const bool recorded = L.pieces && !host_side && ticket % kRecordEvery != 0;
     if (L.pieces) {
-        const bool host_side = src_target == AQUA_TARGET_HOST || dst_target == AQUA_TARGET_HOST;
         L.max_workgroups = p->max_wg[host_side ? AQUA_TARGET_HOST : AQUA_TARGET_DEVICE];
         (void)hipGetLastError();
         e = aqua::launch_copy(L, stream, recorded ? rec.ev : nullptr);
