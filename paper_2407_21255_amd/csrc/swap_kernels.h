@@ -26,6 +26,7 @@ struct SwapLaunch {
     uint32_t max_workgroups;  // 0: as many as part_grid says
     bool nt_pool_store;       // scatter: nontemporal stores into the pool
     bool xcd_order;           // uncapped launches: each XCD takes a contiguous eighth of units
+    bool whole_units;         // a 1024-lane workgroup per unit instead of a wave per KiB
 };
 
 // Scatter store hint, measured on MI355X.  Nontemporal pool stores pay for

@@ -6,8 +6,8 @@
 // waves start.  A unit of work is one run of chunks in one layer; it is cut into
 // parts of about 1 KiB, each copied by a workgroup of one wave with one 16-byte
 // vector per lane, and the parts of a unit stay on one XCD (part_grid).
-// Launches of a capped grid (zero-copy host swaps) use 1024-lane workgroups
-// that loop over whole units with kUnroll = 4 loads per lane in flight.
+// Capped grids (zero-copy host swaps) and large calls in XCD unit order use
+// 1024-lane workgroups that take whole units, kUnroll = 4 loads per lane in flight.
 // The run descriptor is uniform across the workgroup and is fetched with
 // scalar loads.  Cache hints: the offload side is written (swap-out) or read (swap-in) with
 // nontemporal hints: it is touched once and should not displace the pool's
@@ -123,7 +123,7 @@ __device__ __forceinline__ uint32_t run_vectors(const RunDesc& dsc, uint64_t chu
     return (uint32_t)((uint64_t)dsc.nchunks * chunk_bytes / 16);
 }
 
-// Uncapped launches: a wave per part of a unit (part_grid says why).  The loop
+// Most uncapped launches: a wave per part of a unit (part_grid says why).  The loop
 // ends after one pass unless the launch has more parts than a dispatch counts.
 template <bool OUT, bool NT_POOL_ST, typename Get>
 __device__ __forceinline__ void swap_parts(
@@ -142,12 +142,16 @@ __device__ __forceinline__ void swap_parts(
     }
 }
 
-// Capped launches: 1024-lane workgroups that loop over whole units.
+// Whole units to 1024-lane workgroups: capped launches, which loop over them, and
+// those of whole_units, one workgroup per unit.
 template <bool OUT, bool NT_POOL_ST, typename Get>
 __device__ __forceinline__ void swap_units(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const Get& get, uint32_t ndesc,
-    uint32_t l0, uint32_t img_l0, uint32_t units, uint64_t chunk_bytes, uint64_t pool_lstride) {
-    for (uint32_t u = blockIdx.x; u < units; u += gridDim.x) {
+    uint32_t l0, uint32_t img_l0, uint32_t units, uint64_t chunk_bytes, uint64_t pool_lstride,
+    uint32_t xcd_order) {
+    const uint32_t u0 =
+        (xcd_order && gridDim.x == units) ? xcd_unit(blockIdx.x, units) : blockIdx.x;
+    for (uint32_t u = u0; u < units; u += gridDim.x) {
         const uint32_t l = u / ndesc;
         const RunDesc dsc = get(u - l * ndesc);
         swap_unit<OUT, NT_POOL_ST, kMaxThreads>(pool, img, dsc, l0 + l, img_l0,
@@ -169,13 +173,13 @@ __global__ __launch_bounds__(kPartThreads) void swap_runs_kernel(
 }
 
 template <bool OUT, bool NT_POOL_ST>
-__global__ __launch_bounds__(kMaxThreads) void swap_runs_capped_kernel(
+__global__ __launch_bounds__(kMaxThreads) void swap_runs_whole_kernel(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const RunDesc* __restrict__ descs,
     uint32_t ndesc, uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
     uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
     swap_units<OUT, NT_POOL_ST>(
         pool, img, [&](uint32_t k) { return descs[k]; }, ndesc, l0, img_l0, units, chunk_bytes,
-        pool_lstride);
+        pool_lstride, xcd_order);
 }
 
 // and runs in the kernel's arguments, for calls of at most kInlineRuns runs: a
@@ -194,13 +198,13 @@ __global__ __launch_bounds__(kPartThreads) void swap_runs_inline_kernel(
 }
 
 template <bool OUT, bool NT_POOL_ST>
-__global__ __launch_bounds__(kMaxThreads) void swap_runs_inline_capped_kernel(
+__global__ __launch_bounds__(kMaxThreads) void swap_runs_inline_whole_kernel(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const InlineRuns runs, uint32_t ndesc,
     uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
     uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
     swap_units<OUT, NT_POOL_ST>(
         pool, img, [&](uint32_t k) { return unpack_inline(runs.run[k]); }, ndesc, l0, img_l0,
-        units, chunk_bytes, pool_lstride);
+        units, chunk_bytes, pool_lstride, xcd_order);
 }
 
 // Range copy between two offload buffers (image migration): work unit u
@@ -288,10 +292,10 @@ hipError_t launch_with_event(const void* fn, uint32_t grid, uint32_t threads, vo
 template <bool OUT, bool NT_POOL_ST>
 hipError_t launch_swap_k(const SwapLaunch& a, uint32_t l0, uint32_t units, hipStream_t stream,
                          hipEvent_t done) {
-    const bool capped = a.max_workgroups != 0;
+    const bool whole = a.max_workgroups != 0 || a.whole_units;
     const PartGrid g = part_grid(units, a.mean_run_bytes, a.max_run_bytes);
-    const uint32_t grid = capped ? launch_grid(units, a.max_workgroups) : g.grid;
-    const uint32_t threads = capped ? swap_threads(a.chunk_bytes, kMaxThreads) : kPartThreads;
+    const uint32_t grid = whole ? launch_grid(units, a.max_workgroups) : g.grid;
+    const uint32_t threads = whole ? swap_threads(a.chunk_bytes, kMaxThreads) : kPartThreads;
     // The argument array hands the runtime the runs where they are; passed by
     // value they would be copied once more.  The shorter argument is a prefix
     // of the longer one.
@@ -301,10 +305,10 @@ hipError_t launch_swap_k(const SwapLaunch& a, uint32_t l0, uint32_t units, hipSt
                           &units,  &g.parts, &g.total, &a.chunk_bytes, &a.pool_lstride, &xcd};
     const void* fn;
     if (!a.inl)
-        fn = capped ? reinterpret_cast<const void*>(&swap_runs_capped_kernel<OUT, NT_POOL_ST>)
+        fn = whole ? reinterpret_cast<const void*>(&swap_runs_whole_kernel<OUT, NT_POOL_ST>)
                     : reinterpret_cast<const void*>(&swap_runs_kernel<OUT, NT_POOL_ST>);
-    else if (capped)
-        fn = reinterpret_cast<const void*>(&swap_runs_inline_capped_kernel<OUT, NT_POOL_ST>);
+    else if (whole)
+        fn = reinterpret_cast<const void*>(&swap_runs_inline_whole_kernel<OUT, NT_POOL_ST>);
     else if (a.ndesc <= kInlineFew)
         fn = reinterpret_cast<const void*>(&swap_runs_inline_kernel<OUT, NT_POOL_ST, kInlineFew>);
     else
