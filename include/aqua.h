@@ -236,12 +236,13 @@ AQUA_API aqua_status aqua_swap_in_ex(aqua_kv_pool_t pool, uint32_t num_seqs,
  * event or stream.  (Its host-side planning, like that of the other
  * calls, uses ordinary host memory: the pool's planning buffers, which
  * keep the capacity of the largest call seen, and the sort of a swap-in's
- * runs.)  The run descriptors of a call of at most 224 runs travel in its
- * kernel's arguments; those of a larger call go through the pool's pinned ring
- * (allocated when the pool was created; the call never grows it) to a
- * device scratch array of 2 MiB that the library holds on each device for
- * the life of the process.  The completion event is one of the 16 the
- * pool created.  While none is spare (16 calls of the pool in flight), the
+ * runs.)  The run descriptors of a call travel in its kernel's arguments when it
+ * has at most 224 runs, every run's image data starts less than 64 GiB from
+ * the buffer's start and no image is 64 GiB or more per layer.  Those of any
+ * other call go through the pool's pinned ring (allocated when the pool was
+ * created; the call never grows it) to a device scratch array of 2 MiB that
+ * the library holds on each device for the life of the process.  The
+ * completion event is one of the 16 the pool created.  While none is spare (16 calls of the pool in flight), the
  * call first blocks the host until the oldest outstanding call of the pool
  * has completed; a caller that holds its streams from the host must not
  * issue it then.  Differences:
@@ -255,9 +256,11 @@ AQUA_API aqua_status aqua_swap_in_ex(aqua_kv_pool_t pool, uint32_t num_seqs,
  *   - all layers are moved (no layer range or partial image).
  * The scratch array is shared by every pool on a device and keeps the last
  * descriptors written to it.  Calls of this entry point on one pool are ordered
- * with each other by the library; calls of more than 224 runs on
- * different pools of one device that may overlap in time race on the
- * scratch and must be ordered by the caller (one stream, or a sync). */
+ * with each other by the library.  Calls on different pools of one device
+ * that may overlap in time race on the scratch and must be ordered by the
+ * caller (one stream, or a sync), but for those whose descriptors travel in
+ * the arguments: at most 224 runs, and offsets and layers of images below
+ * 64 GiB as above. */
 AQUA_API aqua_status aqua_swap_noalloc(aqua_kv_pool_t pool, int32_t direction,
                                        uint32_t num_seqs, const int32_t* block_ids,
                                        const uint64_t* seq_offsets, void* buf,

@@ -1,9 +1,11 @@
 """How a call's launches are shaped, host core alone (no GPU)."""
 import ctypes
+import os
 
 import numpy as np
 import pytest
 
+from paper_2407_21255_amd import build
 from tests import core_lib
 
 K = 1 << 10
@@ -120,6 +122,29 @@ def test_runs_in_kernel_arguments_keep_every_field(n):
             e = d.copy()
             e[f][n // 2] = top
             assert fits(e) == 0
+
+
+def test_header_states_every_limit_of_runs_in_kernel_arguments():
+    """A caller of the allocation-free entry point has to know which of its
+    calls use the scratch that pools share: the header names both limits, the
+    number of runs and the offset or stride, wherever it names one."""
+    fn = core_lib.lib().aqua_core_inline_round_trip
+    fn.argtypes, fn.restype = [ctypes.c_void_p, ctypes.c_uint64, ctypes.c_void_p], ctypes.c_int32
+
+    def packs(n, off=0, stride=16):
+        d = np.zeros(n, dtype=core_lib.RUN_DESC)
+        d["nchunks"], d["img_off"], d["img_lstride"] = 1, off, stride
+        return fn(d.ctypes.data, n, np.zeros_like(d).ctypes.data) == 1
+
+    runs = max(n for n in range(1, 1025) if packs(n))
+    gib = next(g for g in range(1, 1025) if not packs(1, off=g << 30))
+    assert not packs(1, stride=gib << 30) and packs(1, (gib << 30) - 16, (gib << 30) - 16)
+    text = open(os.path.join(build.INCLUDE, "aqua.h")).read()
+    comment = text[text.index("/* ---- Allocation-free swap"):text.index("aqua_swap_noalloc(")]
+    said = " ".join(comment.replace(" * ", " ").split())
+    assert said.count(f"at most {runs} runs") == 2, said
+    assert said.count(f"{gib} GiB") >= 2, said
+    assert f"more than {runs} runs" not in said
 
 
 @pytest.mark.parametrize("n", [0, 1, 2, 63, 64, 65, 80])
