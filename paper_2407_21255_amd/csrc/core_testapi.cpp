@@ -180,6 +180,20 @@ void aqua_core_part_hits(uint32_t total, uint32_t units, uint32_t parts, uint32_
     }
 }
 
+// The same over a grid of workgroups that take indices a grid apart, counted
+// in 32 bits as the kernels count them.
+void aqua_core_grid_hits(uint32_t grid, uint32_t total, uint32_t units, uint32_t parts,
+                         uint32_t ndesc, const uint32_t* nvec, const uint64_t* base,
+                         uint8_t* hits) {
+    for (uint32_t w = 0; w < grid; ++w)
+        for (uint32_t b = w; b < total; b += grid) {
+            const aqua::UnitPart q = aqua::part_at(b, units, parts);
+            if (q.unit >= units) continue;
+            const aqua::VecRange r = aqua::part_range(nvec[q.unit % ndesc], parts, q.part);
+            for (uint32_t i = 0; i < r.n; ++i) ++hits[base[q.unit] + r.lo + i];
+        }
+}
+
 void* aqua_core_tracker_new(uint32_t num_blocks) {
     return new aqua::HazardTracker(num_blocks);
 }

@@ -57,6 +57,34 @@ def test_parts_cover_every_vector_once(units, lengths):
         assert (hits == 1).all(), parts
 
 
+@pytest.mark.parametrize("units,lengths", [(1, (300,)), (63, (1, 64, 65)), (64, (130,)),
+                                           (130, (1, 64, 65, 700)), (1000, (1,))])
+def test_a_grid_smaller_than_the_launch_covers_it(units, lengths):
+    """Workgroups that take index after index a grid apart (launches of more
+    parts than a dispatch counts) copy every vector once, whatever the grid."""
+    fn = core_lib.lib().aqua_core_grid_hits
+    P = ctypes.c_void_p
+    fn.argtypes, fn.restype = [ctypes.c_uint32] * 5 + [P, P, P], None
+    nvec = np.array(lengths, dtype=np.uint32)
+    per_unit = nvec[np.arange(units) % len(nvec)].astype(np.uint64)
+    base = np.concatenate([[0], np.cumsum(per_unit)]).astype(np.uint64)
+    parts, total, _ = _part_grid(units, int(nvec.mean() * 16), int(nvec.max()) * 16)
+    for grid in sorted({1, 7, 8, 64, max(1, total // 2), max(1, total - 1), total}):
+        hits = np.zeros(int(base[-1]), dtype=np.uint8)
+        fn(grid, total, units, parts, len(nvec), nvec.ctypes.data, base.ctypes.data,
+           hits.ctypes.data)
+        assert (hits == 1).all(), grid
+
+
+@pytest.mark.parametrize("units,mean,longest", [
+    ((1 << 31) - 1, 32, 32), ((1 << 31) - 1, 64 * K, 64 * K), (1 << 25, 2 * K, 2 * K),
+    ((1 << 25) + 1, 16, 16), (430000 * 80, 16, 16), (1 << 20, 64 * K, 1 << 30)])
+def test_the_last_step_of_a_looping_grid_does_not_wrap(units, mean, longest):
+    """An index and one grid more stay below 2^32, in which they are counted."""
+    _, total, grid = _part_grid(units, mean, longest)
+    assert total >= units and total - 1 + grid < 1 << 32
+
+
 def _order(is_in, chunk, blocks, num_blocks, seqs, nbytes):
     fn = core_lib.lib().aqua_core_call_order
     fn.argtypes = [ctypes.c_int32, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32,

@@ -181,18 +181,36 @@ def test_capped_grids_loop_over_every_unit(cap, pinned, chunk_kib):
                max_workgroups=cap or None)
 
 
-def test_more_units_than_one_dispatch_can_count():
+def test_more_units_than_workgroups_of_1024_lanes_can_count():
     """40 layers of a fragmented 131072-block table on a 262144-block pool of
-    32-byte chunks: 5.2 million (layer, run) units, more workgroups than one
-    dispatch can count (its 32-bit work-item count allows 4 194 303 of 1024
-    lanes).  The grid is capped and each workgroup loops over units a grid
-    apart; every byte still matches the oracle."""
+    32-byte chunks: 5.2 million (layer, run) units, more than one dispatch of
+    1024-lane workgroups can count (its 32-bit work-item count allows
+    4 194 303 of them).  Uncapped, each unit is one wave of one pass; capped,
+    each workgroup loops over units a grid apart.  Every byte matches the
+    oracle either way."""
     shape = wl.KVShape(40, 262144, 1, 1, 8, wl.BF16)          # 32-byte chunks
     perm = wl.permutation(shape.num_blocks, 67)
     out_tables = [perm[:131072]]
     in_tables = [perm[131072:]]
-    say("units", shape.num_layers * len(out_tables[0]))
-    _roundtrip(shape, 67, out_tables, in_tables, None)
+    for cap in (None, 4_000_000):
+        say("units", shape.num_layers * len(out_tables[0]), "cap", cap)
+        _roundtrip(shape, 67, out_tables, in_tables, None, max_workgroups=cap)
+
+
+def test_more_units_than_one_dispatch_can_count():
+    """80 layers of a 430000-block table of 16-byte chunks, no two of its
+    blocks adjacent: 34.4 million units of one part each, more than the 2^25
+    one-wave workgroups of a dispatch.  The workgroups take a second index a
+    grid apart; every byte matches the oracle."""
+    shape = wl.KVShape(80, 860064, 1, 1, 8, wl.FP8_E4M3)      # 16-byte chunks, 1.1 GB
+    assert shape.chunk_bytes == 16
+    perm = wl.permutation(shape.num_blocks // 2, 69)
+    n = 430000
+    out_tables = [[2 * b for b in perm[:n]]]
+    in_tables = [[2 * b + 1 for b in perm[-n:]]]
+    assert shape.num_layers * n > 1 << 25
+    say("units", shape.num_layers * n)
+    _roundtrip(shape, 69, out_tables, in_tables, None)
 
 
 def test_layer_ranges_of_32k_chunks_in_xcd_unit_order():
