@@ -260,7 +260,14 @@ AQUA_API aqua_status aqua_swap_in_ex(aqua_kv_pool_t pool, uint32_t num_seqs,
  * that may overlap in time race on the scratch and must be ordered by the
  * caller (one stream, or a sync), but for those whose descriptors travel in
  * the arguments: at most 224 runs, and offsets and layers of images below
- * 64 GiB as above. */
+ * 64 GiB as above.
+ * Capture: a graph may hold one call of a pool (another one of that pool
+ * before the capture ends fails with AQUA_ERR_HIP, and the pool with it).  It
+ * replays the call's copy with the runs it had, however often and whatever the
+ * pool does in between, until the pool is destroyed; the replays are the
+ * caller's to order with the pool's calls.  Descriptors in the ring keep their
+ * place there for that long, so a call that the ring then has no room for is
+ * refused (AQUA_ERR_CAPACITY; aqua_swap_out and aqua_swap_in take new rings). */
 AQUA_API aqua_status aqua_swap_noalloc(aqua_kv_pool_t pool, int32_t direction,
                                        uint32_t num_seqs, const int32_t* block_ids,
                                        const uint64_t* seq_offsets, void* buf,

@@ -148,6 +148,12 @@ struct aqua_kv_pool {
     uint64_t ring_bytes = 0;
     uint64_t ring_head = 0;
     std::deque<RingUse> ring_uses;
+    std::vector<aqua::ByteRange> ring_live;  // scratch of ring_reserve
+    // A graph that captured a call reads the call's descriptors from the ring
+    // at each replay: their space is kept for the life of the pool, also when
+    // the pool goes on with other rings.
+    std::vector<aqua::ByteRange> ring_kept;
+    std::vector<std::pair<uint8_t*, uint8_t*>> kept_rings;  // (device, host)
 
     // Staged host path, per direction (0: swap-out, device to host; 1:
     // swap-in, host to device): two HBM slots and a carrier for the link
@@ -399,36 +405,34 @@ aqua_status alloc_rings(aqua_kv_pool* p, uint64_t bytes) {
 }
 
 // Reserves `bytes` of the descriptor rings, waiting for the calls that used
-// the space last.  Grows the rings when one call needs more than they hold.
+// the space last.  Grows the rings when one call needs more than they hold, and
+// takes new ones when captured calls have left no room in them.
 aqua_status ring_reserve(aqua_kv_pool* p, uint64_t bytes, uint64_t* off, bool grow = true) {
     bytes = (bytes + 255) & ~255ull;
-    if (bytes > p->ring_bytes && !grow) return AQUA_ERR_CAPACITY;
-    if (bytes > p->ring_bytes) {
-        aqua_status st = wait_all(p);
-        if (st != AQUA_OK) return st;
-        uint64_t nb = p->ring_bytes ? p->ring_bytes : kDefaultRingBytes;
-        while (nb < bytes) nb *= 2;
-        free_rings(p);
-        st = alloc_rings(p, nb);
-        if (st != AQUA_OK) return st;
-    }
     // Uses of calls already known complete free their space.  The uses are
     // in allocation order and calls on different streams can complete out
     // of order, so only finished uses at the front are dropped.
     while (!p->ring_uses.empty() && p->tracker.done(p->ring_uses.front().ticket))
         p->ring_uses.pop_front();
-    // Start again at the front of the ring when no live call's descriptors
-    // are there: the host then writes into lines it wrote a few calls ago,
-    // still in its caches.  Walking the whole ring wrote lines evicted long
-    // before, and copying a 135 KB plan into them took about 30 us.
-    bool front_free = true;
-    for (const RingUse& u : p->ring_uses)
-        if (u.lo < bytes) {
-            front_free = false;
-            break;
+    p->ring_live.clear();
+    for (const RingUse& u : p->ring_uses) p->ring_live.emplace_back(u.lo, u.hi);
+    uint64_t lo = 0;
+    if (!aqua::ring_place(p->ring_bytes, bytes, p->ring_head, p->ring_live, p->ring_kept, &lo)) {
+        if (!grow) return AQUA_ERR_CAPACITY;
+        aqua_status st = wait_all(p);
+        if (st != AQUA_OK) return st;
+        uint64_t nb = p->ring_bytes ? p->ring_bytes : kDefaultRingBytes;
+        while (nb < bytes) nb *= 2;
+        if (p->ring_kept.empty()) {
+            free_rings(p);
+        } else {
+            p->kept_rings.emplace_back(p->ring_dev, p->ring_host);
+            p->ring_kept.clear();
+            p->ring_dev = p->ring_host = nullptr;
         }
-    uint64_t lo = p->ring_head;
-    if (front_free || lo + bytes > p->ring_bytes) lo = 0;
+        st = alloc_rings(p, nb);
+        if (st != AQUA_OK) return st;
+    }
     const uint64_t hi = lo + bytes;
     for (;;) {
         bool overlap = false;
@@ -445,6 +449,17 @@ aqua_status ring_reserve(aqua_kv_pool* p, uint64_t bytes, uint64_t* off, bool gr
     p->ring_head = hi;
     *off = lo;
     return AQUA_OK;
+}
+
+// Registers an enqueued call's ring space: free again when the call completes,
+// or, when it was captured, kept for the graph's replays.
+void ring_used(aqua_kv_pool* p, uint64_t off, uint64_t bytes, uint64_t ticket,
+               hipStream_t stream) {
+    const uint64_t hi = off + ((bytes + 255) & ~255ull);
+    p->ring_uses.push_back({off, hi, ticket});
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap != hipStreamCaptureStatusNone) p->ring_kept.emplace_back(off, hi);
 }
 
 // Makes direction dir's staging buffer hold at least `bytes`, waiting for
@@ -1075,7 +1090,7 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
         if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
     }
     p->outstanding[lane].push_back(std::move(rec));
-    if (dbytes) p->ring_uses.push_back({ring_off, ring_off + ((dbytes + 255) & ~255ull), ticket});
+    if (dbytes) ring_used(p, ring_off, dbytes, ticket, stream);
 
     const uint64_t moved = (uint64_t)l_count * total * p->shape.C;
     if (is_in) {
@@ -1234,7 +1249,7 @@ aqua_status do_migrate(aqua_kv_pool* p, const void* src, uint64_t src_bytes, int
         return fail_enqueued(stream, latch(p, e));
     }
     p->outstanding[lane].push_back(std::move(rec));
-    if (dbytes) p->ring_uses.push_back({ring_off, ring_off + ((dbytes + 255) & ~255ull), ticket});
+    if (dbytes) ring_used(p, ring_off, dbytes, ticket, stream);
     p->stats.calls_migrate++;
     p->stats.bytes_migrated += moved;
     if (src_target == AQUA_TARGET_HOST || dst_target == AQUA_TARGET_HOST) p->stats.bytes_host += moved;
@@ -1380,6 +1395,10 @@ aqua_status aqua_kv_pool_destroy(aqua_kv_pool_t p) {
             }
         for (hipEvent_t ev : p->spare_events) (void)hipEventDestroy(ev);
         free_rings(p);
+        for (const auto& r : p->kept_rings) {
+            (void)hipFree(r.first);
+            (void)hipHostFree(r.second);
+        }
         for (int dir = 0; dir < 2; ++dir) {
             if (p->staging[dir]) (void)hipFree(p->staging[dir]);
             if (p->copy[dir]) (void)hipStreamDestroy(p->copy[dir]);

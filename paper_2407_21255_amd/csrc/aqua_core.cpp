@@ -181,6 +181,31 @@ bool pack_inline(const std::vector<RunDesc>& runs, InlineRuns* out) {
     return true;
 }
 
+bool ring_place(uint64_t ring_bytes, uint64_t bytes, uint64_t head,
+                const std::vector<ByteRange>& live, const std::vector<ByteRange>& kept,
+                uint64_t* lo) {
+    auto hit = [](const std::vector<ByteRange>& v, uint64_t at, uint64_t n) {
+        for (const ByteRange& r : v)
+            if (r.first < at + n && at < r.second) return &r;
+        return (const ByteRange*)nullptr;
+    };
+    // The first place from `at` on that leaves every kept range alone.
+    auto from = [&](uint64_t at) {
+        while (at + bytes <= ring_bytes) {
+            const ByteRange* k = hit(kept, at, bytes);
+            if (!k) {
+                *lo = at;
+                return true;
+            }
+            at = k->second;
+        }
+        return false;
+    };
+    if (!from(0)) return false;
+    if (!hit(live, *lo, bytes)) return true;
+    return from(head) || from(0);
+}
+
 uint32_t swap_threads(uint64_t chunk_bytes, uint32_t min_threads) {
     uint32_t lo = 64;
     while (lo < min_threads && lo < kMaxThreads) lo *= 2;

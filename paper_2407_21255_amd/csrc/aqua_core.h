@@ -159,6 +159,18 @@ constexpr RunDesc unpack_inline(const InlineRun& r) {
                    0, 0};
 }
 
+// Where a call's `bytes` of descriptors go in a ring of `ring_bytes`: at the
+// front when no live call's descriptors are there (the host then writes into
+// lines it wrote a few calls ago, still in its caches; walking the whole ring
+// wrote lines evicted long before, and copying a 135 KB plan into them took
+// about 30 us), else at `head`, behind the last call's, or at the front again
+// where that does not fit.  Never over a `kept` range: those are read again by
+// graphs that captured a call.  False when the kept ranges leave no room.
+using ByteRange = std::pair<uint64_t, uint64_t>;
+bool ring_place(uint64_t ring_bytes, uint64_t bytes, uint64_t head,
+                const std::vector<ByteRange>& live, const std::vector<ByteRange>& kept,
+                uint64_t* lo);
+
 // Launch geometry of the copy kernels.  Every lane moves kUnroll 16-byte
 // vectors per pass, so a workgroup of `threads` lanes has threads * 64 bytes
 // in flight.  swap_threads sizes a workgroup so that every lane issues kUnroll

@@ -106,6 +106,18 @@ int32_t aqua_core_call_order(int32_t is_in, uint64_t chunk_bytes, uint64_t block
                                      call_bytes);
 }
 
+// Place of a call's descriptors in a ring; `live` and `kept` hold (lo, hi)
+// pairs.  -1 when kept ranges leave no room.
+int64_t aqua_core_ring_place(uint64_t ring_bytes, uint64_t bytes, uint64_t head,
+                             const uint64_t* live, uint64_t n_live, const uint64_t* kept,
+                             uint64_t n_kept) {
+    std::vector<aqua::ByteRange> l, k;
+    for (uint64_t i = 0; i < n_live; ++i) l.emplace_back(live[2 * i], live[2 * i + 1]);
+    for (uint64_t i = 0; i < n_kept; ++i) k.emplace_back(kept[2 * i], kept[2 * i + 1]);
+    uint64_t lo = 0;
+    return aqua::ring_place(ring_bytes, bytes, head, l, k, &lo) ? (int64_t)lo : -1;
+}
+
 // Packs n 32-byte runs for a kernel's arguments and unpacks them into `out`;
 // 0 if they do not go there.
 int32_t aqua_core_inline_round_trip(const void* descs, uint64_t n, void* out) {

@@ -235,3 +235,36 @@ def test_link_copies_merge_only_where_both_sides_continue():
         assert merged(apart) == apart
     assert merged([(0x100, 0x900, 16), (0x110, 0x910, 16), (0x130, 0x920, 16),
                    (0x140, 0x930, 16)]) == [(0x100, 0x900, 32), (0x130, 0x920, 32)]
+
+
+def test_ring_space_of_captured_calls_is_never_given_out_again():
+    """Random calls over a ring of 64 units, some captured: no call is placed
+    over a captured one's space, a call is refused only where no place avoids
+    them all, and without captured calls the place is the plain rule's (the
+    front if it is free, else behind the last call, else the front)."""
+    fn = core_lib.lib().aqua_core_ring_place
+    P, U64 = ctypes.c_void_p, ctypes.c_uint64
+    fn.argtypes, fn.restype = [U64, U64, U64, P, U64, P, U64], ctypes.c_int64
+    rng = np.random.default_rng(5)
+    for trial in range(200):
+        ring, head, live, kept = 64, 0, [], []
+        for _ in range(60):
+            n = int(rng.integers(1, 70 if rng.random() < 0.1 else 20))
+            la, ka = (np.array(v, dtype=np.uint64).reshape(-1) for v in (live, kept))
+            got = fn(ring, n, head, la.ctypes.data, len(live), ka.ctypes.data, len(kept))
+            free = [a for a in range(ring - n + 1)
+                    if all(h <= a or a + n <= l for l, h in kept)]
+            if not free:
+                assert got == -1
+                continue
+            assert got in free
+            if not kept:
+                front = all(l >= n for l, h in live)
+                assert got == (0 if front or head + n > ring else head)
+            live = [(l, h) for l, h in live if h <= got or got + n <= l]   # waited for
+            live.append((got, got + n))
+            head = got + n
+            if trial % 2 and rng.random() < 0.1:
+                kept.append((got, got + n))
+            while live and rng.random() < 0.4:
+                live.pop(0)

@@ -164,6 +164,98 @@ def test_one_call_captured_and_replayed(entry, runs):
         kv.close()
 
 
+@pytest.mark.parametrize("runs", [20, 150, 240])
+@pytest.mark.parametrize("entry", ["out", "noalloc"])
+def test_replays_between_other_calls_of_the_pool(monkeypatch, entry, runs):
+    """Between the replays of a captured call the pool serves eager calls, of
+    few runs and of more than travel in arguments, on a ring of 768 runs: they
+    take neither the captured call's descriptors nor trouble from its event."""
+    monkeypatch.setenv("AQUA_RING_BYTES", str(24 << 10))
+    shape = wl.KVShape(3, 1024, 1, 16, 64, wl.BF16)            # 4 KiB chunks
+    pool = device_pool(shape, 53)
+    perm = [2 * b for b in wl.permutation(shape.num_blocks // 2, 53)]
+    table, few, many = perm[:runs], perm[40:60], perm[200:500]
+    img, img_few, img_many = (torch.zeros(shape.image_bytes(len(t)), dtype=torch.uint8,
+                                          device="cuda") for t in (table, few, many))
+    kv = aqua.KVPool(shape.as_tuple(), pool)
+
+    def call(t, dst):
+        s = torch.cuda.current_stream()
+        return kv.swap_out([t], dst, stream=s) if entry == "out" else \
+            kv.swap_noalloc(0, [t], dst, stream=s)
+
+    def gathered(t):
+        return pool.view(3, 1024, -1)[:, torch.tensor(t, device="cuda")].reshape(-1)
+
+    try:
+        call(many, img_many)
+        kv.sync()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+            ticket = call(table, img)
+        assert aqua.aqua_query(kv.handle, ticket) == 1   # nothing of it runs yet
+        for k in range(4):
+            say(entry, runs, "replay", k)
+            for _ in range(20):
+                call(few, img_few)
+                call(many, img_many)
+            kv.sync()
+            img.zero_()
+            pool.add_(1)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(img, gathered(table)), k
+            for t, dst in ((few, img_few), (many, img_many)):
+                call(t, dst)
+                kv.sync()
+                assert torch.equal(dst, gathered(t)), k
+    finally:
+        kv.close()
+
+
+def test_captured_calls_fill_the_ring(monkeypatch):
+    """A ring of 384 runs that a captured call of 240 has taken: a call of 300
+    gets new rings, the allocation-free form is refused, and every replay
+    still gathers what was captured."""
+    monkeypatch.setenv("AQUA_RING_BYTES", str(12 << 10))
+    shape = wl.KVShape(3, 1024, 1, 16, 64, wl.BF16)
+    pool = device_pool(shape, 59)
+    perm = [2 * b for b in wl.permutation(shape.num_blocks // 2, 59)]
+    table, many = perm[:240], perm[200:500]
+    img, img_many = (torch.zeros(shape.image_bytes(len(t)), dtype=torch.uint8, device="cuda")
+                     for t in (table, many))
+
+    def gathered(t):
+        return pool.view(3, 1024, -1)[:, torch.tensor(t, device="cuda")].reshape(-1)
+
+    kv = aqua.KVPool(shape.as_tuple(), pool)
+    try:
+        kv.swap_out([many], img_many)
+        kv.sync()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+            kv.swap_out([table], img, stream=torch.cuda.current_stream())
+        with pytest.raises(aqua.AquaError) as e:
+            kv.swap_noalloc(0, [many], img_many)
+        assert e.value.status == aqua.AQUA_ERR_CAPACITY
+        for k in range(3):
+            say("replay", k)
+            img_many.zero_()
+            kv.swap_out([many], img_many)                      # the first takes new rings
+            kv.sync()
+            assert torch.equal(img_many, gathered(many)), k
+            img.zero_()
+            pool.add_(1)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(img, gathered(table)), k
+        kv.swap_noalloc(0, [many], img_many)                   # and they serve it too
+        kv.sync()
+        assert torch.equal(img_many, gathered(many))
+    finally:
+        kv.close()
+
+
 @pytest.mark.parametrize("where", ["hbm", "hbm_capped", "host"])
 @pytest.mark.parametrize("n", [1, 9, 64, 65, 130])
 def test_range_copies_of_few_and_many_ranges(n, where):
