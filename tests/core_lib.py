@@ -81,6 +81,8 @@ def lib():
         L.aqua_core_xcd_unit_order.restype = i32
         L.aqua_core_run_order.argtypes = [i32, u64, u64, u32, u32]
         L.aqua_core_run_order.restype = i32
+        L.aqua_core_call_order.argtypes = [i32, u64, u64, u32, u32, u64]
+        L.aqua_core_call_order.restype = i32
         L.aqua_core_layers_per_launch.argtypes = [u32]
         L.aqua_core_layers_per_launch.restype = u32
         L.aqua_core_launch_grid.argtypes = [u64, u32]
@@ -293,6 +295,12 @@ def interleave_runs(descs: np.ndarray, ways: int) -> np.ndarray:
 
 def xcd_ways() -> int:
     return int(lib().aqua_core_xcd_ways())
+
+
+def call_order(is_in, chunk_bytes: int, blocks: int, num_blocks: int, num_seqs: int,
+               call_bytes: int) -> int:
+    return int(lib().aqua_core_call_order(int(is_in), chunk_bytes, blocks, num_blocks, num_seqs,
+                                          call_bytes))
 
 
 def xcd_unit(block: int, units: int) -> int:

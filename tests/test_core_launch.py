@@ -85,14 +85,6 @@ def test_the_last_step_of_a_looping_grid_does_not_wrap(units, mean, longest):
     assert total >= units and total - 1 + grid < 1 << 32
 
 
-def _order(is_in, chunk, blocks, num_blocks, seqs, nbytes):
-    fn = core_lib.lib().aqua_core_call_order
-    fn.argtypes = [ctypes.c_int32, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_uint32,
-                   ctypes.c_uint32, ctypes.c_uint64]
-    fn.restype = ctypes.c_int32
-    return fn(int(is_in), chunk, blocks, num_blocks, seqs, nbytes)
-
-
 @pytest.mark.parametrize("chunk", [16, 8 * K, 16 * K, 16 * K + 16, 32 * K, 64 * K - 16, 64 * K])
 def test_small_chunk_calls_are_dealt(chunk):
     """Chunks under 64 KiB: swap-outs dealt, swap-ins dealt and, from a
@@ -104,22 +96,22 @@ def test_small_chunk_calls_are_dealt(chunk):
     if chunk == 64 * K:
         for is_in in (0, 1):
             for blocks, n, seqs in ((15, 4096, 1), (512, 4096, 64), (2048, 4096, 1)):
-                assert _order(is_in, chunk, blocks, n, seqs, 4 * G) == \
+                assert core_lib.call_order(is_in, chunk, blocks, n, seqs, 4 * G) == \
                     core_lib.run_order(is_in, chunk, blocks, n, seqs)
         return
     between = 16 * K < chunk
     for seqs in (1, 64):
-        assert _order(0, chunk, 15, 4096, seqs, G) == T
-        assert _order(0, chunk, 16, 4096, seqs, G) == D
-        assert _order(0, chunk, 2048, 4096, seqs, 2 * G - 1) == D
-        assert _order(0, chunk, 2048, 4096, seqs, 2 * G) == (T if between else D)
-        assert _order(1, chunk, 15, 4096, seqs, G) == T
-        assert _order(1, chunk, 255, 4096, seqs, G) == D
-        assert _order(1, chunk, 256, 4096, seqs, G) == S
-        assert _order(1, chunk, 256, 4096, seqs, 2 * G - 1) == S
-        assert _order(1, chunk, 256, 4096, seqs, 2 * G) == (T if between else S)
-        assert _order(1, chunk, 2048, 4096, seqs, 4 * G) == S
-    assert _order(1, chunk, 0, 0, 0, 0) == T
+        assert core_lib.call_order(0, chunk, 15, 4096, seqs, G) == T
+        assert core_lib.call_order(0, chunk, 16, 4096, seqs, G) == D
+        assert core_lib.call_order(0, chunk, 2048, 4096, seqs, 2 * G - 1) == D
+        assert core_lib.call_order(0, chunk, 2048, 4096, seqs, 2 * G) == (T if between else D)
+        assert core_lib.call_order(1, chunk, 15, 4096, seqs, G) == T
+        assert core_lib.call_order(1, chunk, 255, 4096, seqs, G) == D
+        assert core_lib.call_order(1, chunk, 256, 4096, seqs, G) == S
+        assert core_lib.call_order(1, chunk, 256, 4096, seqs, 2 * G - 1) == S
+        assert core_lib.call_order(1, chunk, 256, 4096, seqs, 2 * G) == (T if between else S)
+        assert core_lib.call_order(1, chunk, 2048, 4096, seqs, 4 * G) == S
+    assert core_lib.call_order(1, chunk, 0, 0, 0, 0) == T
 
 
 @pytest.mark.parametrize("n", [0, 1, 223, 224, 225])

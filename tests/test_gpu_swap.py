@@ -162,11 +162,9 @@ def test_unit_size_extremes(unit, monkeypatch):
                                                 (1000, False, 32)])
 def test_capped_grids_loop_over_every_unit(cap, pinned, chunk_kib):
     """A grid capped below the number of (layer, run) units: each workgroup
-    loops over units a grid apart, and every byte still moves once.  With
-    32 KiB chunks the unsorted swap-out asks for the XCD unit order: used on
-    the uncapped grid (cap 0), set aside on a capped one.
-    The swap-ins cover 45 % of the pool, so their runs are sorted and dealt
-    out to the XCDs."""
+    loops over units a grid apart, and every byte still moves once.  The
+    swap-outs' runs are dealt out to the XCDs, in table order; the swap-ins
+    cover 45 % of the pool, so theirs are sorted first."""
     if chunk_kib == 8:
         shape = wl.KVShape(3, 512, 2, 16, 64, wl.BF16)
     else:
@@ -213,13 +211,12 @@ def test_more_units_than_one_dispatch_can_count():
     _roundtrip(shape, 69, out_tables, in_tables, None)
 
 
-def test_layer_ranges_of_32k_chunks_in_xcd_unit_order():
-    """32 KiB chunks to an HBM buffer, 1.4 GiB each way: the swap-outs keep
-    table order and run in the kernels' XCD unit order over the units of
-    their layer range; the swap-ins cover 49 % of the pool, so their runs
-    are sorted and dealt out to the XCDs.  Whole calls and layer ranges
-    (1-7, 4-5, 9) match the oracle byte for byte, guard bytes included, and
-    each call is one launch."""
+def test_layer_ranges_of_dealt_32k_chunks():
+    """32 KiB chunks to an HBM buffer, 1.4 GiB each way: the swap-outs' runs
+    are dealt out to the XCDs in table order, the swap-ins', which cover 49 %
+    of the pool, sorted first.  Whole calls and layer ranges (1-7, 4-5, 9)
+    match the oracle byte for byte, guard bytes included, and each call is
+    one launch."""
     shape = wl.KVShape(10, 9216, 8, 16, 128, wl.FP8_E4M3)    # 32 KiB chunks, 2.8 GiB
     C = shape.chunk_bytes
     assert C == 32 << 10
@@ -252,6 +249,53 @@ def test_layer_ranges_of_32k_chunks_in_xcd_unit_order():
                                      l0, nl) == 0
             assert_bytes_equal(host(buf), want, f"image after layers {layers}")
             assert_bytes_equal(host(pool), pool_h, f"pool after layers {layers}")
+    finally:
+        kv.close()
+        del pool, buf
+        torch.cuda.empty_cache()
+
+
+def test_layer_ranges_of_32k_chunks_in_xcd_unit_order():
+    """32 KiB chunks to an HBM buffer, a third of the pool in calls of 2 GiB
+    and more: both directions keep table order and take whole units in the
+    kernels' XCD unit order (on the uncapped grid; a capped one sets it
+    aside), over all layers and over a proper layer range of 2 GiB that
+    starts past the first.  Byte for byte the oracle's, guard bytes
+    included, one launch each."""
+    from tests import core_lib
+    shape = wl.KVShape(9, 25000, 8, 16, 128, wl.FP8_E4M3)    # 32 KiB chunks, 6.9 GiB
+    C, n = shape.chunk_bytes, 8200
+    perm = wl.permutation(shape.num_blocks, 73)
+    out_t = [perm[:5000], perm[5000:5001], perm[5001:n]]
+    in_t = [perm[n:n + 5000], perm[n + 5000:n + 5001], perm[n + 5001:2 * n]]
+    d = odesc(shape)
+    pool = device_pool(shape, 73)
+    pool_h = host(pool)
+    size = shape.image_bytes(n)
+    buf = guarded_buffer(size, G)
+    inner = buf[G:G + size]
+    want = np.full(size + 2 * G, wl.GUARD_BYTE, dtype=np.uint8)
+    kv = aqua.KVPool(shape.as_tuple(), pool)
+    try:
+        for l0, nl, cap in [(0, 9, 0), (1, 8, 0), (1, 8, 1000)]:
+            kv.set_max_workgroups(aqua.AQUA_TARGET_DEVICE, cap)
+            assert nl * n * C >= 2 << 30
+            for is_in in (0, 1):
+                assert core_lib.call_order(is_in, C, n, shape.num_blocks, 3, nl * n * C) == \
+                    core_lib.TABLE
+            assert core_lib.xcd_unit_order(C, False)
+            say("32 KiB layer ranges, XCD unit order, layers", l0, nl, "cap", cap)
+            before = kv.stats()["launches"]
+            kv.swap_out(out_t, inner, layers=(l0, nl))
+            kv.swap_in(in_t, inner, layers=(l0, nl))
+            kv.sync()
+            assert kv.stats()["launches"] == before + 2
+            assert oracle.swap_out_ex(d, pool_h, out_t, want[G:G + size], None, None, l0, nl) == 0
+            assert oracle.swap_in_ex(d, pool_h, in_t, want[G:G + size], None, None, l0, nl) == 0
+            assert_bytes_equal(host(buf), want, f"image after layers {l0}, {nl}")
+            assert_bytes_equal(host(pool), pool_h, f"pool after layers {l0}, {nl}")
+            pool.view(torch.int64).add_(1)       # other bytes for the next range
+            pool_h.view(np.int64)[:] += 1
     finally:
         kv.close()
         del pool, buf
