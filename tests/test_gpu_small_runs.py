@@ -1,6 +1,6 @@
 """GPU parity of swaps of small chunks and of few runs, against the oracle byte
-for byte: every workgroup width, at chunk sizes on and beside its edges; runs
-in the kernels' arguments, at and beside the number that goes there; and the
+for byte: chunk sizes on and beside the edges of a wave's 1 KiB and of a row of
+1024 lanes; runs in the kernels' arguments, at and beside the number that goes there; and the
 descriptor ring, with calls that need it."""
 import numpy as np
 import pytest
@@ -28,9 +28,9 @@ def _gpu():
 @pytest.mark.parametrize("long_runs", [False, True], ids=["single", "mixed"])
 @pytest.mark.parametrize("chunk", [16, 1008, 1024, 1040, 2048, 2064, 4096, 4112, 6144, 8192,
                                    12288, 16368, 16384])
-def test_every_width_at_its_edges(chunk, long_runs):
-    """Single-block runs, and single blocks beside stretches of up to 64 KiB
-    whose runs are longer than the mean that sizes the workgroup."""
+def test_parts_of_a_run_at_their_edges(chunk, long_runs):
+    """Single-block runs, and single blocks beside stretches of up to 64 KiB,
+    whose runs have more parts of 1 KiB than the others."""
     shape = wl.KVShape(3, 600, 1, 1, chunk // 2, wl.FP8_E4M3)
     assert shape.chunk_bytes == chunk
     perm = wl.permutation(200, 91)
