@@ -154,7 +154,8 @@ def test_header_states_every_limit_of_runs_in_kernel_arguments():
     def packs(n, off=0, stride=16):
         d = np.zeros(n, dtype=core_lib.RUN_DESC)
         d["nchunks"], d["img_off"], d["img_lstride"] = 1, off, stride
-        return fn(d.ctypes.data, n, np.zeros_like(d).ctypes.data) == 1
+        got = np.zeros_like(d)
+        return fn(d.ctypes.data, n, got.ctypes.data) == 1
 
     runs = max(n for n in range(1, 1025) if packs(n))
     gib = next(g for g in range(1, 1025) if not packs(1, off=g << 30))
