@@ -631,9 +631,9 @@ def test_errors_match_oracle_and_leave_no_trace():
                 kv.swap_out([[1]], b, target=target)
             assert ei.value.status == aqua.AQUA_ERR_INVALID
         # A buffer size beyond its allocation is refused, not written.
-        st, _ = aqua.aqua_swap_out(kv.handle, 1, np.array([1], np.int32).ctypes.data,
-                                   np.array([0, 1], np.uint64).ctypes.data, buf.data_ptr(),
-                                   1 << 40, None, 0, None)
+        ids, offs = np.array([1], np.int32), np.array([0, 1], np.uint64)
+        st, _ = aqua.aqua_swap_out(kv.handle, 1, ids.ctypes.data, offs.ctypes.data,
+                                   buf.data_ptr(), 1 << 40, None, 0, None)
         assert st == aqua.AQUA_ERR_INVALID
         torch.cuda.synchronize()
         assert_bytes_equal(host(pool), pool_h, "pool after failing calls")
