@@ -640,8 +640,7 @@ aqua::SwapLaunch make_launch(aqua_kv_pool* p, bool is_in, uint8_t* img, const Ru
                                           p->call_dealt);
     L.mean_run_bytes = p->call_blocks * p->shape.C / std::max<uint32_t>(1, ndesc);
     L.max_run_bytes = p->call_max_run * p->shape.C;
-    L.xcd_order = false;
-    L.whole_units = false;
+    L.xcd_units = false;
     return L;
 }
 
@@ -1065,13 +1064,13 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
             aqua::SwapLaunch L =
                 make_launch(p, is_in, dbuf, reinterpret_cast<const RunDesc*>(descs),
                             (uint32_t)p->plan.size(), target, l_begin, l_count);
-            L.xcd_order = target == AQUA_TARGET_DEVICE && aqua::xcd_unit_order(p->shape.C, dealt);
             // Large calls in that order are a scheduler's slices, two at a time
             // on two streams, which mix worse cut to a wave per KiB: the fp8
             // preemption cycle, 2 GiB each way, took 1584-1587 us so and
             // 1509 us with whole units.
-            L.whole_units = L.xcd_order &&
-                            (uint64_t)l_count * total * p->shape.C >= aqua::kXcdUnitMinBytes;
+            L.xcd_units = target == AQUA_TARGET_DEVICE &&
+                          aqua::xcd_unit_order(p->shape.C, dealt) &&
+                          (uint64_t)l_count * total * p->shape.C >= aqua::kXcdUnitMinBytes;
             recorded = !zero_copy && ticket % kRecordEvery != 0;
             if (recorded && !rec.ev) e = take_event(p, &rec.ev);
             if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));

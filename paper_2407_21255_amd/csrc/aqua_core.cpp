@@ -206,15 +206,6 @@ bool ring_place(uint64_t ring_bytes, uint64_t bytes, uint64_t head,
     return from(head) || from(0);
 }
 
-uint32_t swap_threads(uint64_t chunk_bytes, uint32_t min_threads) {
-    uint32_t lo = 64;
-    while (lo < min_threads && lo < kMaxThreads) lo *= 2;
-    uint32_t t = lo;
-    const uint64_t want = chunk_bytes / (16ull * kUnroll);  // lanes for one pass
-    while (t < kMaxThreads && t < want) t *= 2;
-    return t;
-}
-
 PartGrid part_grid(uint32_t units, uint64_t mean_run_bytes, uint64_t max_run_bytes) {
     const uint64_t slots = units < kSpreadUnits ? units : ((uint64_t)units + 7) / 8 * 8;
     auto pieces = [](uint64_t bytes) {

@@ -171,16 +171,11 @@ bool ring_place(uint64_t ring_bytes, uint64_t bytes, uint64_t head,
                 const std::vector<ByteRange>& live, const std::vector<ByteRange>& kept,
                 uint64_t* lo);
 
-// Launch geometry of the copy kernels.  Every lane moves kUnroll 16-byte
-// vectors per pass, so a workgroup of `threads` lanes has threads * 64 bytes
-// in flight.  swap_threads sizes a workgroup so that every lane issues kUnroll
-// loads before its first store: 1024 lanes for 64 KiB and more, fewer for
-// less (down to min_threads, a power of two of at least 64).  Launches of a
-// capped grid, whose workgroups loop over units, ask for the full 1024: there a
-// workgroup's lanes are what is in flight.
+// Launch geometry of the copy kernels.  A lane moves kUnroll 16-byte vectors
+// per pass, its loads all issued before its first store, where a workgroup has
+// as many for it: one of kMaxThreads lanes has 64 KiB in flight.
 constexpr uint32_t kUnroll = 4;
 constexpr uint32_t kMaxThreads = 1024;
-uint32_t swap_threads(uint64_t chunk_bytes, uint32_t min_threads);
 
 // How an uncapped swap launch splits its units: each unit, one (layer, run), is
 // cut into `parts` of about 1 KiB, each the work of a workgroup of one wave, one

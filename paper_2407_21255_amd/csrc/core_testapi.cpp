@@ -356,10 +356,6 @@ void aqua_core_tracker_soak(uint64_t n_calls, uint32_t num_blocks, uint32_t stre
     }
 }
 
-uint32_t aqua_core_swap_threads(uint64_t chunk_bytes, uint32_t min_threads) {
-    return aqua::swap_threads(chunk_bytes, min_threads);
-}
-
 // Sorts n descriptors (32 bytes each) in place by block with sort_by_block.
 void aqua_core_sort_by_block(void* descs, uint64_t n, uint32_t num_blocks) {
     std::vector<aqua::RunDesc> v(n), tmp;

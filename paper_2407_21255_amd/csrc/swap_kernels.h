@@ -25,8 +25,8 @@ struct SwapLaunch {
     uint64_t max_run_bytes;
     uint32_t max_workgroups;  // 0: as many as part_grid says
     bool nt_pool_store;       // scatter: nontemporal stores into the pool
-    bool xcd_order;           // uncapped launches: each XCD takes a contiguous eighth of units
-    bool whole_units;         // a 1024-lane workgroup per unit instead of a wave per KiB
+    bool xcd_units;           // a 1024-lane workgroup per unit instead of a wave per KiB,
+                              // and to each XCD a contiguous eighth of the units
 };
 
 // Scatter store hint, measured on MI355X.  Nontemporal pool stores pay for

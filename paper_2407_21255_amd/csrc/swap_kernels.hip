@@ -100,9 +100,9 @@ __device__ __forceinline__ void copy_span(const v4u* __restrict__ s,
 // Work unit u in [0, units) is (layer l0 + u / ndesc, descriptor u % ndesc);
 // layer l of the image side starts img_l0 layers before img_off's origin
 // (0 for whole images, the first staged layer for a staging slot).  In
-// plain order consecutive workgroups take consecutive units; with xcd_order
-// each XCD takes a contiguous eighth of them (xcd_unit), and the host may
-// have dealt each layer's runs out to the XCDs already (interleave_runs).
+// plain order consecutive workgroups take consecutive units, whose runs the
+// host may have dealt out to the XCDs (interleave_runs); with xcd_units each
+// XCD takes a contiguous eighth of the units (xcd_unit).
 // One unit: vectors [r.lo, r.lo + r.n) of run dsc in layer l.
 template <bool OUT, bool NT_POOL_ST, int THREADS>
 __device__ __forceinline__ void swap_unit(uint8_t* __restrict__ pool, uint8_t* __restrict__ img,
@@ -129,13 +129,12 @@ template <bool OUT, bool NT_POOL_ST, typename Get>
 __device__ __forceinline__ void swap_parts(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const Get& get, uint32_t ndesc,
     uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
-    uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
+    uint64_t chunk_bytes, uint64_t pool_lstride) {
     for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {
         const UnitPart q = part_at(b, units, parts);
         if (q.unit >= units) continue;
-        const uint32_t u = xcd_order ? xcd_unit(q.unit, units) : q.unit;
-        const uint32_t l = u / ndesc;
-        const RunDesc dsc = get(u - l * ndesc);
+        const uint32_t l = q.unit / ndesc;
+        const RunDesc dsc = get(q.unit - l * ndesc);
         const VecRange r = part_range(run_vectors(dsc, chunk_bytes), parts, q.part);
         swap_unit<OUT, NT_POOL_ST, kPartThreads>(pool, img, dsc, l0 + l, img_l0, r, chunk_bytes,
                                                  pool_lstride);
@@ -143,14 +142,14 @@ __device__ __forceinline__ void swap_parts(
 }
 
 // Whole units to 1024-lane workgroups: capped launches, which loop over them, and
-// those of whole_units, one workgroup per unit.
+// those in XCD unit order, one workgroup per unit.
 template <bool OUT, bool NT_POOL_ST, typename Get>
 __device__ __forceinline__ void swap_units(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const Get& get, uint32_t ndesc,
     uint32_t l0, uint32_t img_l0, uint32_t units, uint64_t chunk_bytes, uint64_t pool_lstride,
-    uint32_t xcd_order) {
+    uint32_t xcd_units) {
     const uint32_t u0 =
-        (xcd_order && gridDim.x == units) ? xcd_unit(blockIdx.x, units) : blockIdx.x;
+        (xcd_units && gridDim.x == units) ? xcd_unit(blockIdx.x, units) : blockIdx.x;
     for (uint32_t u = u0; u < units; u += gridDim.x) {
         const uint32_t l = u / ndesc;
         const RunDesc dsc = get(u - l * ndesc);
@@ -166,20 +165,20 @@ template <bool OUT, bool NT_POOL_ST>
 __global__ __launch_bounds__(kPartThreads) void swap_runs_kernel(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const RunDesc* __restrict__ descs,
     uint32_t ndesc, uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
-    uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
+    uint64_t chunk_bytes, uint64_t pool_lstride) {
     swap_parts<OUT, NT_POOL_ST>(
         pool, img, [&](uint32_t k) { return descs[k]; }, ndesc, l0, img_l0, units, parts, total,
-        chunk_bytes, pool_lstride, xcd_order);
+        chunk_bytes, pool_lstride);
 }
 
 template <bool OUT, bool NT_POOL_ST>
 __global__ __launch_bounds__(kMaxThreads) void swap_runs_whole_kernel(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const RunDesc* __restrict__ descs,
-    uint32_t ndesc, uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
-    uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
+    uint32_t ndesc, uint32_t l0, uint32_t img_l0, uint32_t units, uint64_t chunk_bytes,
+    uint64_t pool_lstride, uint32_t xcd_units) {
     swap_units<OUT, NT_POOL_ST>(
         pool, img, [&](uint32_t k) { return descs[k]; }, ndesc, l0, img_l0, units, chunk_bytes,
-        pool_lstride, xcd_order);
+        pool_lstride, xcd_units);
 }
 
 // and runs in the kernel's arguments, for calls of at most kInlineRuns runs: a
@@ -191,20 +190,20 @@ template <bool OUT, bool NT_POOL_ST, uint32_t CAP>
 __global__ __launch_bounds__(kPartThreads) void swap_runs_inline_kernel(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const InlineArg<CAP> runs,
     uint32_t ndesc, uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
-    uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
+    uint64_t chunk_bytes, uint64_t pool_lstride) {
     swap_parts<OUT, NT_POOL_ST>(
         pool, img, [&](uint32_t k) { return unpack_inline(runs.run[k]); }, ndesc, l0, img_l0,
-        units, parts, total, chunk_bytes, pool_lstride, xcd_order);
+        units, parts, total, chunk_bytes, pool_lstride);
 }
 
 template <bool OUT, bool NT_POOL_ST>
 __global__ __launch_bounds__(kMaxThreads) void swap_runs_inline_whole_kernel(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const InlineRuns runs, uint32_t ndesc,
-    uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
-    uint64_t chunk_bytes, uint64_t pool_lstride, uint32_t xcd_order) {
+    uint32_t l0, uint32_t img_l0, uint32_t units, uint64_t chunk_bytes, uint64_t pool_lstride,
+    uint32_t xcd_units) {
     swap_units<OUT, NT_POOL_ST>(
         pool, img, [&](uint32_t k) { return unpack_inline(runs.run[k]); }, ndesc, l0, img_l0,
-        units, chunk_bytes, pool_lstride, xcd_order);
+        units, chunk_bytes, pool_lstride, xcd_units);
 }
 
 // Range copy between two offload buffers (image migration): work unit u
@@ -292,17 +291,20 @@ hipError_t launch_with_event(const void* fn, uint32_t grid, uint32_t threads, vo
 template <bool OUT, bool NT_POOL_ST>
 hipError_t launch_swap_k(const SwapLaunch& a, uint32_t l0, uint32_t units, hipStream_t stream,
                          hipEvent_t done) {
-    const bool whole = a.max_workgroups != 0 || a.whole_units;
+    const bool whole = a.max_workgroups != 0 || a.xcd_units;
     const PartGrid g = part_grid(units, a.mean_run_bytes, a.max_run_bytes);
     const uint32_t grid = whole ? launch_grid(units, a.max_workgroups) : g.grid;
-    const uint32_t threads = whole ? swap_threads(a.chunk_bytes, kMaxThreads) : kPartThreads;
+    const uint32_t threads = whole ? kMaxThreads : kPartThreads;
     // The argument array hands the runtime the runs where they are; passed by
     // value they would be copied once more.  The shorter argument is a prefix
     // of the longer one.
-    const uint32_t xcd = a.xcd_order;
+    const uint32_t xcd = a.xcd_units;
     const void* runs = a.inl ? (const void*)a.inl : (const void*)&a.descs;
-    const void* args[] = {&a.pool, &a.img,   runs,     &a.ndesc,       &l0,             &a.img_l0,
-                          &units,  &g.parts, &g.total, &a.chunk_bytes, &a.pool_lstride, &xcd};
+    const void* part_args[] = {&a.pool,   &a.img, runs,     &a.ndesc, &l0,
+                               &a.img_l0, &units, &g.parts, &g.total, &a.chunk_bytes,
+                               &a.pool_lstride};
+    const void* whole_args[] = {&a.pool,   &a.img, runs,           &a.ndesc,        &l0,
+                                &a.img_l0, &units, &a.chunk_bytes, &a.pool_lstride, &xcd};
     const void* fn;
     if (!a.inl)
         fn = whole ? reinterpret_cast<const void*>(&swap_runs_whole_kernel<OUT, NT_POOL_ST>)
@@ -313,7 +315,8 @@ hipError_t launch_swap_k(const SwapLaunch& a, uint32_t l0, uint32_t units, hipSt
         fn = reinterpret_cast<const void*>(&swap_runs_inline_kernel<OUT, NT_POOL_ST, kInlineFew>);
     else
         fn = reinterpret_cast<const void*>(&swap_runs_inline_kernel<OUT, NT_POOL_ST, kInlineRuns>);
-    return launch_with_event(fn, grid, threads, const_cast<void**>(args), stream, done);
+    return launch_with_event(fn, grid, threads,
+                             const_cast<void**>(whole ? whole_args : part_args), stream, done);
 }
 
 }  // namespace

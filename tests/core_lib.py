@@ -70,8 +70,6 @@ def lib():
         L.aqua_core_lanes_size.restype = u64
         L.aqua_core_tracker_soak.argtypes = [u64, u32, u32, u64, u32, ctypes.POINTER(u64),
                                              ctypes.POINTER(u64)]
-        L.aqua_core_swap_threads.argtypes = [u64, u32]
-        L.aqua_core_swap_threads.restype = u32
         L.aqua_core_sort_by_block.argtypes = [P, u64, u32]
         L.aqua_core_interleave_runs.argtypes = [P, u64, u32]
         L.aqua_core_xcd_ways.restype = u32
@@ -252,10 +250,6 @@ class LaneMap:
         if getattr(self, "h", None):
             lib().aqua_core_lanes_free(self.h)
             self.h = None
-
-
-def swap_threads(chunk_bytes: int, min_threads: int) -> int:
-    return int(lib().aqua_core_swap_threads(chunk_bytes, min_threads))
 
 
 def launch_grid(units: int, max_workgroups: int) -> int:

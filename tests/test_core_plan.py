@@ -212,28 +212,6 @@ def test_launch_grid_stays_within_one_dispatch():
     assert launch_grid(0, 0) == 0
 
 
-def test_workgroup_is_sized_to_the_chunk():
-    """Every lane holds 4 vectors of 16 bytes in flight: a 64 KiB chunk
-    takes 1024 lanes, 32 KiB 512, 16 KiB 256; a larger chunk still 1024,
-    and smaller ones never go below the minimum asked for (a power of two
-    of at least one wave)."""
-    from tests.core_lib import swap_threads
-    assert swap_threads(64 << 10, 64) == 1024
-    assert swap_threads(1 << 20, 64) == 1024
-    assert swap_threads(32 << 10, 64) == 512
-    assert swap_threads(16 << 10, 64) == 256
-    assert swap_threads(4 << 10, 64) == 64
-    assert swap_threads(48 << 10, 64) == 1024   # 768 lanes' worth rounds up
-    assert swap_threads(32, 64) == 64
-    assert swap_threads(16 << 10, 256) == 256
-    assert swap_threads(4 << 10, 256) == 256
-    assert swap_threads(4 << 10, 200) == 256
-    assert swap_threads(32 << 10, 1024) == 1024
-    for c in (16, 32, 4096, 12288, 65536, 1 << 30):
-        t = swap_threads(c, 64)
-        assert t in (64, 128, 256, 512, 1024)
-
-
 def test_run_order_rule():
     """Chunks of 64 KiB or more: every swap-in sorted by pool block and
     dealt out to the XCDs; a swap-out dealt in table order when it covers at
