@@ -99,7 +99,7 @@ uint8_t* scratch_address(int device) {
 
 struct Outstanding {
     uint64_t ticket;
-    hipEvent_t ev;                 // recorded on the call's stream, last
+    hipEvent_t ev;                 // completes last of the call, on its stream
     std::vector<hipEvent_t> aux;   // events inside the call (staging slots)
 };
 
@@ -1035,7 +1035,7 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
         p->stats.waits_inserted++;
     }
 
-    bool recorded = false;  // the call's event is on its kernel
+    bool on_launch = false;  // the call's event rides on its kernel's launch
     if (!p->plan.empty()) {
         hipError_t e = hipSuccess;
         const uint8_t* descs = nullptr;
@@ -1071,11 +1071,11 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
             L.xcd_units = target == AQUA_TARGET_DEVICE &&
                           aqua::xcd_unit_order(p->shape.C, dealt) &&
                           (uint64_t)l_count * total * p->shape.C >= aqua::kXcdUnitMinBytes;
-            recorded = !zero_copy && ticket % kRecordEvery != 0;
-            if (recorded && !rec.ev) e = take_event(p, &rec.ev);
+            on_launch = !zero_copy && ticket % kRecordEvery != 0;
+            if (on_launch && !rec.ev) e = take_event(p, &rec.ev);
             if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
             (void)hipGetLastError();
-            e = aqua::launch_swap(L, stream, &p->stats.launches, recorded ? rec.ev : nullptr);
+            e = aqua::launch_swap(L, stream, &p->stats.launches, on_launch ? rec.ev : nullptr);
             if (e != hipSuccess) {
                 give_back();
                 return fail_enqueued(stream, latch(p, e));
@@ -1083,7 +1083,7 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
         }
     }
 
-    if (!recorded) {
+    if (!on_launch) {
         hipError_t e = rec.ev ? hipSuccess : take_event(p, &rec.ev);
         if (e == hipSuccess) e = hipEventRecord(rec.ev, stream);
         if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
@@ -1236,13 +1236,13 @@ aqua_status do_migrate(aqua_kv_pool* p, const void* src, uint64_t src_bytes, int
     hipError_t e = take_event(p, &rec.ev);
     if (e != hipSuccess) return fail_enqueued(stream, latch(p, e));
     const bool host_side = src_target == AQUA_TARGET_HOST || dst_target == AQUA_TARGET_HOST;
-    const bool recorded = L.pieces && !host_side && ticket % kRecordEvery != 0;
+    const bool on_launch = L.pieces && !host_side && ticket % kRecordEvery != 0;
     if (L.pieces) {
         L.max_workgroups = p->max_wg[host_side ? AQUA_TARGET_HOST : AQUA_TARGET_DEVICE];
         (void)hipGetLastError();
-        e = aqua::launch_copy(L, stream, recorded ? rec.ev : nullptr);
+        e = aqua::launch_copy(L, stream, on_launch ? rec.ev : nullptr);
     }
-    if (e == hipSuccess && !recorded) e = hipEventRecord(rec.ev, stream);
+    if (e == hipSuccess && !on_launch) e = hipEventRecord(rec.ev, stream);
     if (e != hipSuccess) {
         p->spare_events.push_back(rec.ev);
         return fail_enqueued(stream, latch(p, e));
