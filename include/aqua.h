@@ -312,7 +312,8 @@ AQUA_API aqua_status aqua_stream_wait(aqua_kv_pool_t pool, uint64_t ticket,
 AQUA_API aqua_status aqua_query(aqua_kv_pool_t pool, uint64_t ticket);
 
 /* Cap the number of workgroups of later kernel launches for one target
- * (0: no cap, one workgroup per (layer, run)).  For the host target the cap
+ * (0: no cap, about one 64-lane workgroup per KiB of a (layer, run), or one
+ * of 1024 lanes per (layer, run); capped, workgroups of 1024 lanes).  For the host target the cap
  * applies to zero-copy swaps; staged swaps gather in HBM without a cap. */
 AQUA_API aqua_status aqua_kv_pool_set_max_workgroups(aqua_kv_pool_t pool,
                                             int32_t target,
@@ -392,10 +393,13 @@ AQUA_API const char* aqua_status_str(aqua_status s);
  *
  * The swap kernels' roofline is HBM bandwidth, read plus write (a swap with
  * an HBM offload target reads and writes every payload byte once).  These
- * calls run the swap kernels' own copy loop -- 64 KiB per 1024-lane
- * workgroup, four 16-byte vectors per lane in flight, nontemporal hints --
- * over one contiguous range, so that a caller can measure, in the same run
- * and on the same device, what a copy, a pure read and a pure write reach:
+ * calls run the copy loop of the range copies and of swaps that take whole
+ * runs -- 64 KiB per 1024-lane workgroup, four 16-byte vectors per lane in
+ * flight, nontemporal hints -- over one contiguous range, so that a caller can
+ * measure, in the same run and on the same device, what a copy, a pure read
+ * and a pure write reach in that shape.  They are yardsticks, not ceilings: most
+ * swaps run a wave per KiB, which moves more than the copy does (6.4 against
+ * 5.7 TB/s of traffic at 10 GiB on MI355X).
  *   AQUA_YARDSTICK_COPY   copies bytes from src to dst (ranges disjoint);
  *   AQUA_YARDSTICK_READ   reads bytes of src; dst (16 bytes at least) is
  *                         not written for any input a caller can give

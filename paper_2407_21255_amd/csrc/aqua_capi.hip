@@ -184,7 +184,7 @@ struct aqua_kv_pool {
     uint64_t next_ticket = 1;
     uint64_t unit_bytes = kDefaultUnitBytes;
     uint8_t* scratch = nullptr;  // this device's scratch (aqua_swap_noalloc)
-    // Grid caps per target (0: one workgroup per unit).  Zero-copy host
+    // Grid caps per target (0: as many workgroups as part_grid says).  Zero-copy host
     // swaps are link-bound: 16 workgroups of 1024 lanes saturate the link.
     uint32_t max_wg[2] = {0, kHostZeroCopyWorkgroups};
     aqua_pool_stats stats{};
@@ -1064,10 +1064,7 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
             aqua::SwapLaunch L =
                 make_launch(p, is_in, dbuf, reinterpret_cast<const RunDesc*>(descs),
                             (uint32_t)p->plan.size(), target, l_begin, l_count);
-            // Large calls in that order are a scheduler's slices, two at a time
-            // on two streams, which mix worse cut to a wave per KiB: the fp8
-            // preemption cycle, 2 GiB each way, took 1584-1587 us so and
-            // 1509 us with whole units.
+            // The calls that call_order leaves in table order for it.
             L.xcd_units = target == AQUA_TARGET_DEVICE &&
                           aqua::xcd_unit_order(p->shape.C, dealt) &&
                           (uint64_t)l_count * total * p->shape.C >= aqua::kXcdUnitMinBytes;

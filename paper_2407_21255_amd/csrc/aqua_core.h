@@ -115,7 +115,7 @@ struct LinkPiece {
     uint64_t bytes;
 };
 // Appends a copy, as part of the last one where it continues that on both
-// sides: a copy engine spends about 20 us on each copy beyond its bytes, so 36
+// sides: a copy engine spends about 34 us on each copy beyond its bytes, so 36
 // sequences of 1.2 MiB took 1.2 ms more than one copy of them all.
 void append_piece(std::vector<LinkPiece>* v, const LinkPiece& p);
 
@@ -243,7 +243,7 @@ uint32_t launch_grid(uint64_t units, uint32_t max_workgroups);
 //     other call keeps table order.
 // Sorted, the pool side of consecutive units moves through the pool in
 // address order and the image side jumps; in table order the reverse.
-// Measured on MI355X, same box:
+// Measured on MI355X, same box, with one 1024-lane workgroup per unit:
 //   swap-ins (pool written in order), calls covering half the pool: sorted
 //     against table order, 70B scatter 3.3 % shorter, one TP2 rank's 1.6 %,
 //     one TP4 rank's 2.8 %; a sixteenth of the pool (8B, fp8 8B): no gain,
@@ -260,6 +260,11 @@ uint32_t launch_grid(uint64_t units, uint32_t max_workgroups);
 //     gather of 64 prompts of 16 blocks too cost it 8 %, hence the 32-block
 //     mean.  Sorting or dealing sparse calls of smaller chunks lost 2.6 %
 //     (the fp8 8B pair, whose scatter then leaves the XCD unit order).
+// With a wave per KiB the orders lie closer (64 KiB chunks, 32 layers, three
+// processes): swap-outs dealt against table order 1 % longer to 4 % shorter at
+// 128 MiB to 3 GiB, 32 sequences of 16 blocks 1 % shorter and no longer slower;
+// swap-ins sorted and dealt against dealt alone within 1 %, against table order
+// within 1 % at 256 MiB, 1-2 % shorter at 1 GiB, 0-2 % at 3 GiB.
 enum class RunOrder { kTable, kSortedDealt, kTableDealt };
 constexpr uint64_t kDenseMinPermille = 400;     // share of the pool's blocks
 constexpr uint64_t kDealMinChunk = 64ull << 10;
@@ -268,21 +273,48 @@ RunOrder run_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t n
                    uint32_t num_seqs);
 
 // run_order refined by the bytes a call of chunks under 64 KiB moves, for the
-// calls that run_order leaves in table order.  With workgroups sized to the runs
-// and nontemporal stores (nt_pool_store), dealing pays there too.  Measured on
-// MI355X, 32 layers, one and 16 sequences, a third and an eighth of the pool,
-// cold caches, against table order (and, between 16 and 64 KiB, the XCD unit
-// order) with ordinary scatter stores:
-//   swap-outs, dealt in table order: 128 MiB 0-11 % shorter, 512 MiB 0-24 %
-//     (the 24 % with 16 sequences), 2 GiB 0-8 %; against the XCD unit order
-//     2-14 % at 128 MiB, 0-6 % at 512 MiB, within 3 % from 2 GiB on;
-//   swap-ins, dealt: 128 MiB 5-22 % shorter, 512 MiB 3-25 %; sorted first as
-//     well, another 0-6 % from 512 MiB on, nothing below.  The sort is O(runs +
-//     pool blocks), so only calls that cover a sixteenth of the pool take it.
-//   2 GiB and more, chunks between 16 and 64 KiB, a small part of the pool: the
-//     XCD unit order is 2-12 % shorter for swap-ins than sorted and dealt, and
-//     within 3 % for swap-outs (the fp8 preemption cycle 0.7 % shorter), so
-//     those calls keep it.
+// calls that run_order leaves in table order.  Measured on MI355X with a wave
+// per KiB, 32 layers, one and 16 sequences, a third to a twentieth of the pool,
+// calls one after another on cold buffers, three processes:
+//   swap-outs, dealt in table order: 128 MiB to 2.2 GiB within 2.5 % of table
+//     order for chunks to 16 KiB, 3 % shorter to 1 % longer for 32 KiB; against whole units
+//     in XCD unit order (32 KiB chunks) 3-9 % shorter at 128 MiB, 1-5 % at
+//     512 MiB, 1-3 % at 1 GiB, within 1 % at 2.2 GiB;
+//   swap-ins, dealt against table order: 2 KiB chunks 1 % shorter to 3 % longer,
+//     8 KiB within 2 %, 16 KiB 0-4 % and 32 KiB 1-5 % shorter; against whole
+//     units in XCD unit order (32 KiB) 0-9 % shorter up to 1 GiB;
+//   swap-ins, sorted as well, against dealt alone: 1-4 % longer at 128 MiB; from
+//     512 MiB on 8 to 32 KiB chunks 2-7 % shorter for a third and a twelfth of
+//     the pool, 4 % shorter to 3 % longer for a twentieth; 2 KiB chunks 0-5 %
+//     longer, for a twentieth 34-92 % (the sort, O(runs + pool blocks), then
+//     outlasts the copy).  So only calls that cover a sixteenth of the pool
+//     sort.
+//
+// Calls of 2 GiB and more in chunks between 16 and 64 KiB that cover less than
+// 40 % of the pool keep table order, and the kernels take whole units of them in
+// XCD unit order (xcd_unit).  The line is drawn for a scheduler's slices, a
+// swap-out beside a swap-in on two streams: the fp8 preemption cycle (32 KiB
+// chunks, 2.05 GiB each way, sequences of very different lengths) took 1584 us
+// with a wave per KiB in that order, 1583 dealt, 1509 so.  Lone calls and even
+// slices, three processes, whole units in XCD unit order against
+//                              24 KiB         32 KiB         48 KiB chunks
+//   a wave per KiB in that order
+//     swap-out, 2.1-5 GiB      2-3 % shorter  3-4 % shorter  0-1 % shorter
+//     swap-in                  -3 to +3 %     within 1 %     3 % longer
+//     both at once             0-4 % shorter  2-4 % shorter  1 % longer
+//   dealt (swap-outs and swap-ins), a wave per KiB
+//     swap-out                 within 2 %     -2 to +1 %     1-3 % longer
+//     swap-in, 2.1-3 GiB       4-6 % longer   1-3 % longer   5-6 % longer
+//     both at once             -4 to +2 %     0-2 % shorter  2-3 % longer
+//   sorted and dealt swap-ins
+//     swap-in, 2.1-3 GiB       3-6 % longer   8-10 % longer  4-6 % longer
+//     both at once             3-7 % shorter  1-6 % shorter  1-2 % shorter
+// (In one of the three processes 24 KiB swap-ins of 3 GiB in XCD unit order were
+// 11 % shorter than dealt, in all three those of 5 GiB of an eighth of the pool.)
+// A lone swap-in of that size would gain from being sorted and dealt, by which a
+// slice would lose; the rule does not tell them apart.  Below 2 GiB lone calls
+// are as short dealt or shorter, and slices of 24 and 48 KiB chunks 1-3 % shorter;
+// those of 32 KiB chunks are 1-3 % longer (1.9 GiB 1340 against 1305 us).
 // The bytes are the whole call's.
 constexpr uint64_t kXcdUnitMinBytes = 2ull << 30;
 constexpr uint64_t kSortMinShare = 16;  // a sixteenth of the pool's blocks
@@ -319,19 +351,15 @@ void sort_by_block(std::vector<RunDesc>* runs, uint32_t num_blocks,
 constexpr uint32_t kXcdWays = 8;
 void interleave_runs(std::vector<RunDesc>* runs, uint32_t ways, std::vector<RunDesc>* tmp);
 
-// XCD-aware unit order inside the kernels, for calls whose runs are not
-// dealt out.  On a launch of one workgroup per unit, workgroup b (sent to XCD
-// (b + c) % 8, c fixed for the launch) takes unit xcd_unit(b, units), so that
-// each XCD copies one contiguous eighth of the launch's units in order (the
-// (b % 8)-th eighth; the first units % 8 eighths hold one unit more).  A
-// bijection on [0, units).  Used for undealt calls of chunks between 16 and 64 KiB
-// (exclusive) to an HBM buffer, where it measured, against plain order on
-// the same box (3 to 4 runs each, with launches of at most 512 MiB then):
-// the fp8 preemption cycle +4.2 %, one TP2 rank +0.5 %, the fp8 8B pair
-// +0.5 %; on the fp8 8B pool, one prompt of
-// 1024 or 2048 blocks +3 to +8 %, 64 short prompts +1 to +16 %, the gather of
-// 8 prompts -0.4 to -1.9 %.  With 64 KiB chunks it slowed 64 short prompts by
-// 6 %, with 16 KiB chunks a TP4 rank by 1.2 %, so those keep plain order.
+// XCD-aware unit order inside the kernels, on a launch of one workgroup per
+// unit: workgroup b (sent to XCD (b + c) % 8, c fixed for the launch) takes unit
+// xcd_unit(b, units), so that each XCD copies one contiguous eighth of the
+// launch's units in order (the (b % 8)-th eighth; the first units % 8 eighths
+// hold one unit more).  A bijection on [0, units).  For undealt calls of 2 GiB
+// and more, chunks between 16 and 64 KiB (exclusive), to an HBM buffer; call_order
+// says what it measures there.  When every undealt call was of one 1024-lane
+// workgroup per unit, it cost 64 KiB chunks 6 % (64 short prompts) and 16 KiB
+// chunks 1.2 % (a TP4 rank), so those never take it.
 constexpr uint32_t xcd_unit(uint32_t block, uint32_t units) {
     const uint32_t x = block % kXcdWays, q = units / kXcdWays, r = units % kXcdWays;
     return x * q + (x < r ? x : r) + block / kXcdWays;

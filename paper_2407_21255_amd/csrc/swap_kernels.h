@@ -29,23 +29,26 @@ struct SwapLaunch {
                               // and to each XCD a contiguous eighth of the units
 };
 
-// Scatter store hint, measured on MI355X.  Nontemporal pool stores pay for
-// large chunks and for calls that write much more than the 256 MB last-level
-// cache holds.  A smaller call of smaller chunks ends sooner with ordinary
-// stores, which L2 and that cache partly absorb:
-//   64 KiB chunks: 0-7 % shorter with nontemporal stores, 2 to 10 GiB calls;
-//   32 KiB chunks: 10 % longer at 1 GiB per call, 0.5-2 % shorter at 4.4-5 GiB;
-//   16 KiB chunks: 20 % longer at 512 MiB per call, 7 % shorter at 2.5 GiB.
-// The bytes are the whole call's, also when several launches carry it: ordinary
-// stores chosen for each 512 MiB launch of a larger call made its scatter
-// 2-15 % longer.
-// Runs dealt out to the XCDs turn the smaller calls round: each XCD then
-// writes one contiguous stretch of a layer.  Dealt scatters of 2 to 32 KiB
-// chunks, nontemporal against ordinary stores: 256 MiB to 1 GiB 10-16 %
-// shorter.  Below the 256 MB of the last-level cache it depends on what
-// follows: one call after another, 64 MiB 6-10 % and 128 MiB 11-13 % shorter;
-// a call by itself, whose stores the cache absorbs, 8-14 % longer (198 MiB 99
-// against 86 us).  Those keep ordinary stores.
+// Scatter store hint: nontemporal pool stores for chunks of 64 KiB and more, for
+// calls of 2 GiB and more and for dealt calls of 256 MiB and more.  Measured on
+// MI355X with a wave per KiB, nontemporal against ordinary stores: sorted and
+// dealt swap-ins of an eighth of a 32-layer pool, three processes.
+//   One call after another over 1 GiB of images and blocks in turn, so that the
+//   caches hold nothing of the next: 64 KiB chunks 5-12 % shorter at every size
+//   from 32 MiB to 3 GiB; 8 to 32 KiB chunks 8-12 % from 32 to 512 MiB, 10-15 %
+//   at 1 and 3 GiB; 2 KiB chunks the same at 32 and 64 MiB, 9-11 % shorter from
+//   128 MiB.  Each call waited for before the next: 0-5 % shorter up to 64 MiB,
+//   4-11 % from 128 MiB.
+//   The same call again and again on the same buffers, whose stores the 256 MB
+//   last-level cache absorbs: 64 MiB 0-7 % longer, 128 to 256 MiB 4-16 %
+//   longer (198 MiB of 16 KiB chunks 74.4 against 64.7 us; 64 KiB chunks 5-11 %),
+//   512 MiB 5-12 % shorter.
+//   Table order, 1 and 3 GiB: 4-8 % shorter.
+// So the 256 MiB line is where ordinary stores end to win on cached buffers, and
+// below it they lose on cold ones.  The 2 GiB line is older than the dealing:
+// undealt calls of fewer bytes and smaller chunks keep ordinary stores, but
+// only those of fewer than 16 blocks are left undealt there.
+// The bytes are the whole call's for an HBM buffer, a slot's for the staged path.
 constexpr uint64_t kNtPoolStoreMinChunk = 64ull << 10;
 constexpr uint64_t kNtPoolStoreMinBytes = 2ull << 30;
 constexpr uint64_t kNtPoolStoreMinDealt = 256ull << 20;

@@ -234,8 +234,8 @@ __global__ __launch_bounds__(kMaxThreads) void copy_ranges_inline_kernel(
     copy_pieces(src, dst, [&](uint32_t u) { return piece_of(ranges, count, u); }, n);
 }
 
-// HBM yardsticks over nvec contiguous vectors, in 64 KiB pieces with the
-// swap kernels' lane shape and hints.  MODE 0 copies src to dst, MODE 1 only
+// HBM yardsticks over nvec contiguous vectors, in 64 KiB pieces with the lane
+// shape and hints of whole-unit swap launches.  MODE 0 copies src to dst, MODE 1 only
 // reads src (the vectors are folded together and stored to dst only if the
 // fold equals a key no real input produces, so the loads stay), MODE 2 only
 // writes dst: vector i holds {i low, i high, key, ~key}.
