@@ -277,9 +277,9 @@ RunOrder run_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t n
 // per KiB, 32 layers, one and 16 sequences, a third to a twentieth of the pool,
 // calls one after another on cold buffers, three processes:
 //   swap-outs, dealt in table order: 128 MiB to 2.2 GiB within 2.5 % of table
-//     order for chunks to 16 KiB, 3 % shorter to 1 % longer for 32 KiB; against whole units
-//     in XCD unit order (32 KiB chunks) 3-9 % shorter at 128 MiB, 1-5 % at
-//     512 MiB, 1-3 % at 1 GiB, within 1 % at 2.2 GiB;
+//     order for chunks to 16 KiB, 3 % shorter to 1 % longer for 32 KiB; against
+//     whole units in XCD unit order (32 KiB chunks) 3-9 % shorter at 128 MiB,
+//     1-5 % at 512 MiB, 1-3 % at 1 GiB, within 1 % at 2.2 GiB;
 //   swap-ins, dealt against table order: 2 KiB chunks 1 % shorter to 3 % longer,
 //     8 KiB within 2 %, 16 KiB 0-4 % and 32 KiB 1-5 % shorter; against whole
 //     units in XCD unit order (32 KiB) 0-9 % shorter up to 1 GiB;
@@ -290,9 +290,9 @@ RunOrder run_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t n
 //     outlasts the copy).  So only calls that cover a sixteenth of the pool
 //     sort.
 //
-// Calls of 2 GiB and more in chunks between 16 and 64 KiB that cover less than
-// 40 % of the pool keep table order, and the kernels take whole units of them in
-// XCD unit order (xcd_unit).  The line is drawn for a scheduler's slices, a
+// Calls of 2 GiB and more in chunks between 16 and 64 KiB, swap-outs and those
+// swap-ins that cover less than 40 % of the pool, keep table order, and the
+// kernels take whole units of them in XCD unit order (xcd_unit).  The line is drawn for a scheduler's slices, a
 // swap-out beside a swap-in on two streams: the fp8 preemption cycle (32 KiB
 // chunks, 2.05 GiB each way, sequences of very different lengths) took 1584 us
 // with a wave per KiB in that order, 1583 dealt, 1509 so.  Lone calls and even
