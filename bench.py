@@ -441,8 +441,9 @@ def run_pair(args, res_common):
 
 
 def hbm_ceiling(dst, src, reps: int = 5) -> dict:
-    """Same-run HBM yardsticks of the payload's size with the library's own
-    copy loop (aqua_hbm_yardstick): a contiguous copy (GB/s of read + write
+    """Same-run HBM yardsticks of the payload's size with the copy loop of the
+    library's 1024-lane workgroups (aqua_hbm_yardstick; swaps that run a wave
+    per KiB go beyond its copy): a contiguous copy (GB/s of read + write
     traffic), a pure read and a pure write, each timed with HIP events on
     its launch stream after one untimed pass; each as a share of 8 TB/s.
     ``serial`` is the rate of reading the payload and then writing it, one

@@ -69,7 +69,7 @@ hipError_t launch_swap(const SwapLaunch& a, hipStream_t stream, uint64_t* launch
                        hipEvent_t done = nullptr);
 
 // Enqueues one HBM yardstick over `bytes` (a multiple of 16) of device
-// memory with the swap kernels' copy loop: mode 0 copies src to dst, mode 1
+// memory with the copy loop of whole-unit swaps and range copies: mode 0 copies src to dst, mode 1
 // reads src only, mode 2 writes dst only (see aqua_hbm_yardstick).
 hipError_t launch_yardstick(int mode, const uint8_t* src, uint8_t* dst, uint64_t bytes,
                             uint32_t key, hipStream_t stream);
