@@ -179,7 +179,8 @@ struct aqua_kv_pool {
     std::vector<uint64_t> slot_offsets;  // per sequence, in a slot
     uint64_t call_blocks = 0;            // table entries of the call being enqueued
     bool call_dealt = false;             // its runs are dealt out to the XCDs
-    uint64_t call_max_run = 0;           // blocks of its longest run
+    uint64_t call_min_run = 0;           // blocks of its shortest run
+    uint64_t call_max_run = 0;           // and of its longest
 
     uint64_t next_ticket = 1;
     uint64_t unit_bytes = kDefaultUnitBytes;
@@ -639,6 +640,7 @@ aqua::SwapLaunch make_launch(aqua_kv_pool* p, bool is_in, uint8_t* img, const Ru
     L.nt_pool_store = aqua::nt_pool_store(p->shape.C, (uint64_t)nl * p->call_blocks * p->shape.C,
                                           p->call_dealt);
     L.mean_run_bytes = p->call_blocks * p->shape.C / std::max<uint32_t>(1, ndesc);
+    L.min_run_bytes = p->call_min_run * p->shape.C;
     L.max_run_bytes = p->call_max_run * p->shape.C;
     L.xcd_units = false;
     return L;
@@ -941,8 +943,12 @@ aqua_status do_swap(aqua_kv_pool* p, bool is_in, uint32_t num_seqs,
         aqua::sort_by_block(&p->plan, p->shape.N, &p->sort_counts, &p->sort_tmp);
     const bool dealt = order != aqua::RunOrder::kTable;
     p->call_dealt = dealt;
+    p->call_min_run = p->plan.empty() ? 0 : p->plan[0].nchunks;
     p->call_max_run = 0;
-    for (const RunDesc& r : p->plan) p->call_max_run = std::max<uint64_t>(p->call_max_run, r.nchunks);
+    for (const RunDesc& r : p->plan) {
+        p->call_min_run = std::min<uint64_t>(p->call_min_run, r.nchunks);
+        p->call_max_run = std::max<uint64_t>(p->call_max_run, r.nchunks);
+    }
     if (dealt) aqua::interleave_runs(&p->plan, aqua::kXcdWays, &p->sort_tmp);
     aqua::image_ranges(p->shape, a, &p->ranges);
     for (auto& r : p->ranges) {  // tracked by the caller's address of the buffer

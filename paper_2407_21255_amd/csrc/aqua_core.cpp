@@ -206,14 +206,18 @@ bool ring_place(uint64_t ring_bytes, uint64_t bytes, uint64_t head,
     return from(head) || from(0);
 }
 
-PartGrid part_grid(uint32_t units, uint64_t mean_run_bytes, uint64_t max_run_bytes) {
+PartGrid part_grid(uint32_t units, uint64_t min_run_bytes, uint64_t mean_run_bytes,
+                   uint64_t max_run_bytes) {
     const uint64_t slots = units < kSpreadUnits ? units : ((uint64_t)units + 7) / 8 * 8;
     auto pieces = [](uint64_t bytes) {
         return std::max<uint64_t>(1, bytes / kPartBytes + (bytes % kPartBytes != 0));
     };
     // 16384 waves fill the chip twice.
     uint64_t parts = pieces(max_run_bytes);
-    if (slots * parts > 16384) parts = std::min(parts, pieces(mean_run_bytes));
+    if (slots * parts > 16384) {
+        const bool few_longer = (mean_run_bytes - min_run_bytes) * 8 < min_run_bytes;
+        parts = std::min(parts, pieces(few_longer ? min_run_bytes : mean_run_bytes));
+    }
     while (parts > 1 && slots * parts > kMaxPartGrid) parts = (parts + 1) / 2;
     PartGrid g;
     g.parts = (uint32_t)parts;

@@ -173,10 +173,15 @@ uint64_t aqua_core_append_pieces(const uint64_t* in, uint64_t n, uint64_t* out) 
 }
 
 void aqua_core_part_grid(uint32_t units, uint64_t mean_bytes, uint64_t max_bytes, uint32_t* out) {
-    const aqua::PartGrid g = aqua::part_grid(units, mean_bytes, max_bytes);
+    const aqua::PartGrid g = aqua::part_grid(units, 0, mean_bytes, max_bytes);
     out[0] = g.parts;
     out[1] = g.total;
     out[2] = g.grid;
+}
+
+uint32_t aqua_core_parts(uint32_t units, uint64_t min_bytes, uint64_t mean_bytes,
+                         uint64_t max_bytes) {
+    return aqua::part_grid(units, min_bytes, mean_bytes, max_bytes).parts;
 }
 
 // Copies bytes as the part kernels would, index by index: adds 1 to

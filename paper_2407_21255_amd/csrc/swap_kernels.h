@@ -21,6 +21,7 @@ struct SwapLaunch {
     uint32_t num_layers;
     uint64_t chunk_bytes;     // C
     uint64_t pool_lstride;    // N * C
+    uint64_t min_run_bytes;
     uint64_t mean_run_bytes;  // per layer
     uint64_t max_run_bytes;
     uint32_t max_workgroups;  // 0: as many as part_grid says

@@ -292,7 +292,7 @@ template <bool OUT, bool NT_POOL_ST>
 hipError_t launch_swap_k(const SwapLaunch& a, uint32_t l0, uint32_t units, hipStream_t stream,
                          hipEvent_t done) {
     const bool whole = a.max_workgroups != 0 || a.xcd_units;
-    const PartGrid g = part_grid(units, a.mean_run_bytes, a.max_run_bytes);
+    const PartGrid g = part_grid(units, a.min_run_bytes, a.mean_run_bytes, a.max_run_bytes);
     const uint32_t grid = whole ? launch_grid(units, a.max_workgroups) : g.grid;
     const uint32_t threads = whole ? kMaxThreads : kPartThreads;
     // The argument array hands the runtime the runs where they are; passed by

@@ -36,6 +36,21 @@ def test_a_wave_per_kib_of_a_run(units, mean, longest, want):
     assert grid * 64 < 1 << 32 and total >= units and total % parts == 0
 
 
+@pytest.mark.parametrize("units,shortest,mean,longest,parts", [
+    # One pair of adjacent blocks among 2047 runs of a block; 16 pairs among 4096.
+    (163760, 16 * K, 16 * K + 8, 32 * K, 16), (130560, K, K + 4, 2 * K, 1),
+    (65535, 1280, 1281, 2560, 2), (65535, 64 * K, 64 * K, 64 * K, 64),
+    # Up to an eighth more than the shortest, and from there on, the mean.
+    (65536, 8 * K, 9 * K - 16, 64 * K, 8), (65536, 8 * K, 9 * K, 64 * K, 9),
+    # Most runs long, some short: the mean as before; few waves: the longest.
+    (65536, 8 * K, 63 * K + 16, 64 * K, 64), (100, 16 * K, 16 * K + 8, 32 * K, 32)])
+def test_few_longer_runs_give_the_others_no_empty_part(units, shortest, mean, longest, parts):
+    fn = core_lib.lib().aqua_core_parts
+    fn.argtypes = [ctypes.c_uint32] + [ctypes.c_uint64] * 3
+    fn.restype = ctypes.c_uint32
+    assert fn(units, shortest, mean, longest) == parts
+
+
 @pytest.mark.parametrize("units", [1, 2, 7, 63, 64, 65, 71, 72, 130])
 @pytest.mark.parametrize("lengths", [(1,), (64,), (65,), (4096,), (1, 64, 65, 700, 4096), (640, 641)])
 def test_parts_cover_every_vector_once(units, lengths):
