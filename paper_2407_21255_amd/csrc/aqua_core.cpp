@@ -246,7 +246,8 @@ RunOrder call_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t 
         blocks < 2 * kXcdWays)
         return o;
     if (call_bytes >= kXcdUnitMinBytes && xcd_unit_order(chunk_bytes, false)) return o;
-    const bool sorted = is_in && blocks * kSortMinShare >= num_blocks;
+    const bool sorted = is_in && blocks * kSortMinShare >= num_blocks &&
+                        call_bytes >= kSortMinBytes && call_bytes / blocks >= kSortMinRow;
     return sorted ? RunOrder::kSortedDealt : RunOrder::kTableDealt;
 }
 

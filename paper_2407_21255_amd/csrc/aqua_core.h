@@ -293,8 +293,13 @@ RunOrder run_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t n
 //     512 MiB on 8 to 32 KiB chunks 2-7 % shorter for a third and a twelfth of
 //     the pool, 4 % shorter to 3 % longer for a twentieth; 2 KiB chunks 0-5 %
 //     longer, for a twentieth 34-92 % (the sort, O(runs + pool blocks), then
-//     outlasts the copy).  So only calls that cover a sixteenth of the pool
-//     sort.
+//     outlasts the copy).  On another box, 4 to 80 layers, sorted within 3 % of
+//     dealt alone from 256 MiB on where a block has 256 KiB over all layers, 2-5 %
+//     longer below 256 MiB; where a block has 128 KiB 1 % shorter to 5 % longer,
+//     and with 32 KiB (8 KiB chunks in 4 layers) up to 13 % longer, 64 MiB 81
+//     against 31 us.  A call waited for takes the sort's time longer.  So only
+//     calls that cover a sixteenth of the pool sort, of 256 MiB and more, with
+//     256 KiB and more to a block.
 //
 // Calls of 2 GiB and more in chunks between 16 and 64 KiB, swap-outs and those
 // swap-ins that cover less than 40 % of the pool, keep table order, and the
@@ -324,6 +329,8 @@ RunOrder run_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t n
 // The bytes are the whole call's.
 constexpr uint64_t kXcdUnitMinBytes = 2ull << 30;
 constexpr uint64_t kSortMinShare = 16;  // a sixteenth of the pool's blocks
+constexpr uint64_t kSortMinBytes = 256ull << 20;
+constexpr uint64_t kSortMinRow = 256ull << 10;  // a block's bytes over the call's layers
 RunOrder call_order(bool is_in, uint64_t chunk_bytes, uint64_t blocks, uint32_t num_blocks,
                     uint32_t num_seqs, uint64_t call_bytes);
 

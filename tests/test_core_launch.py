@@ -129,6 +129,20 @@ def test_small_chunk_calls_are_dealt(chunk):
     assert core_lib.call_order(1, chunk, 0, 0, 0, 0) == T
 
 
+@pytest.mark.parametrize("layers,chunk,blocks,num_blocks,sorts", [
+    (4, 8 * K, 2828, 36898, False),      # 88 MiB: the sort outlasts the copy
+    (4, 8 * K, 32768, 131072, False),    # 1 GiB of 32 KiB blocks
+    (16, 8 * K, 8192, 65536, False),     # 1 GiB of 128 KiB blocks
+    (32, 8 * K, 1023, 8192, False), (32, 8 * K, 1024, 8192, True),     # 256 MiB, 256 KiB
+    (31, 8 * K, 2048, 8192, False), (32, 8 * K, 1024, 16384, True), (32, 8 * K, 1024, 16385, False),
+    (4, 8 * K, 32768, 65536, True), (4, 8 * K, 26214, 65536, False)])  # 40 %: run_order's rule
+def test_only_calls_that_gain_by_it_are_sorted(layers, chunk, blocks, num_blocks, sorts):
+    """Swap-ins of small chunks that cover less than 40 % of the pool: sorted
+    from a sixteenth of it, 256 MiB and 256 KiB to a block, else dealt."""
+    got = core_lib.call_order(1, chunk, blocks, num_blocks, 1, layers * blocks * chunk)
+    assert got == (core_lib.SORTED_DEALT if sorts else core_lib.TABLE_DEALT)
+
+
 @pytest.mark.parametrize("n", [0, 1, 223, 224, 225])
 def test_runs_in_kernel_arguments_keep_every_field(n):
     """What a kernel reads from its arguments is the run that was planned, at
