@@ -190,6 +190,7 @@ constexpr uint32_t kMaxThreads = 1024;
 // more vectors per lane 2-7 %.
 // The parts of a unit go to the XCD the whole unit would go to (part_at), so
 // that dealt runs stay dealt; below kSpreadUnits units they go to all XCDs.
+constexpr uint32_t kXcdWays = 8;  // a launch's workgroups go to the 8 XCDs in turn
 constexpr uint64_t kPartBytes = 1ull << 10;
 constexpr uint32_t kPartThreads = 64;
 constexpr uint32_t kSpreadUnits = 64;
@@ -210,6 +211,20 @@ struct PartGrid {
 // run is over eight ninths of the mean, it decides.
 PartGrid part_grid(uint32_t units, uint64_t min_run_bytes, uint64_t mean_run_bytes,
                    uint64_t max_run_bytes);
+// Units of one layer in such a launch, `ndesc` runs and padding: with a multiple
+// of eight, run k goes to the same XCD in every layer.  Otherwise the XCDs take
+// another eighth of the runs in each layer, and where the runs are read from the
+// pinned ring each XCD fetches most of them over the link, all its waves
+// waiting.  Measured on MI355X, runs of 8 to 96 KiB, 1 to 5 beyond a multiple
+// of eight, padded against not: 4 layers 0-12 % shorter from 233 runs
+// on (4091 runs of 64 KiB, 403 -> 360 us), 32 layers 0-3 %, 80 layers within
+// 1 %; 1 GiB of 1 KiB runs in 32 layers 668 -> 464 us.  Runs in the kernel's
+// arguments, at most kInlineRuns, only pay for the padding: 65 runs 1-7 % longer,
+// 129 runs 0-4 %.
+constexpr uint32_t kAlignRuns = 256;
+constexpr uint32_t layer_units(uint32_t ndesc) {
+    return ndesc < kAlignRuns ? ndesc : (ndesc + kXcdWays - 1) / kXcdWays * kXcdWays;
+}
 struct UnitPart {
     uint32_t unit, part;  // unit >= units: padding, nothing to do
 };
@@ -361,7 +376,6 @@ void sort_by_block(std::vector<RunDesc>* runs, uint32_t num_blocks,
 // its turn at another XCD than the first (where the previous launch left
 // off); that only changes which XCD takes which eighth.  Runs only ever
 // change order, so no byte changes.  `tmp` is reusable scratch.
-constexpr uint32_t kXcdWays = 8;
 void interleave_runs(std::vector<RunDesc>* runs, uint32_t ways, std::vector<RunDesc>* tmp);
 
 // XCD-aware unit order inside the kernels, on a launch of one workgroup per

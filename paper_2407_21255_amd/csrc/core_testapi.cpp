@@ -211,6 +211,24 @@ void aqua_core_grid_hits(uint32_t grid, uint32_t total, uint32_t units, uint32_t
         }
 }
 
+// Over a launch of `layers` layers of ndesc runs: adds 1 to hits[l * ndesc + k]
+// for each unit that reaches run k of layer l, and returns 0 if a run's unit
+// goes to another XCD in one layer than in the next.
+int32_t aqua_core_layer_hits(uint32_t layers, uint32_t ndesc, uint8_t* hits) {
+    const uint32_t row = aqua::layer_units(ndesc), units = layers * row;
+    std::vector<uint32_t> xcd(ndesc, ~0u);
+    int32_t same = 1;
+    const uint32_t total = units < aqua::kSpreadUnits ? units : (units + 7) / 8 * 8;
+    for (uint32_t b = 0; b < total; ++b) {
+        const uint32_t u = aqua::part_at(b, units, 1).unit;
+        if (u >= units || u % row >= ndesc) continue;
+        ++hits[u / row * ndesc + u % row];
+        if (xcd[u % row] != ~0u && xcd[u % row] != b % 8) same = 0;
+        xcd[u % row] = b % 8;
+    }
+    return same;
+}
+
 void* aqua_core_tracker_new(uint32_t num_blocks) {
     return new aqua::HazardTracker(num_blocks);
 }

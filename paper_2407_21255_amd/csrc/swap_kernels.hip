@@ -97,10 +97,10 @@ __device__ __forceinline__ void copy_span(const v4u* __restrict__ s,
 
 // OUT: pool -> image (gather).  !OUT: image -> pool (scatter), with
 // nontemporal pool stores when NT_POOL_ST.
-// Work unit u in [0, units) is (layer l0 + u / ndesc, descriptor u % ndesc);
-// layer l of the image side starts img_l0 layers before img_off's origin
-// (0 for whole images, the first staged layer for a staging slot).  In
-// plain order consecutive workgroups take consecutive units, whose runs the
+// Work unit u in [0, units) is (layer l0 + u / row, descriptor u % row), where
+// row is ndesc or, with padding, layer_units(ndesc); layer l of the image side
+// starts img_l0 layers before img_off's origin (0 for whole images, the first
+// staged layer for a staging slot).  In plain order consecutive workgroups take consecutive units, whose runs the
 // host may have dealt out to the XCDs (interleave_runs); with xcd_units each
 // XCD takes a contiguous eighth of the units (xcd_unit).
 // One unit: vectors [r.lo, r.lo + r.n) of run dsc in layer l.
@@ -128,13 +128,13 @@ __device__ __forceinline__ uint32_t run_vectors(const RunDesc& dsc, uint64_t chu
 template <bool OUT, bool NT_POOL_ST, typename Get>
 __device__ __forceinline__ void swap_parts(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const Get& get, uint32_t ndesc,
-    uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
+    uint32_t row, uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
     uint64_t chunk_bytes, uint64_t pool_lstride) {
     for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {
         const UnitPart q = part_at(b, units, parts);
-        if (q.unit >= units) continue;
-        const uint32_t l = q.unit / ndesc;
-        const RunDesc dsc = get(q.unit - l * ndesc);
+        const uint32_t l = q.unit / row, k = q.unit - l * row;
+        if (q.unit >= units || k >= ndesc) continue;
+        const RunDesc dsc = get(k);
         const VecRange r = part_range(run_vectors(dsc, chunk_bytes), parts, q.part);
         swap_unit<OUT, NT_POOL_ST, kPartThreads>(pool, img, dsc, l0 + l, img_l0, r, chunk_bytes,
                                                  pool_lstride);
@@ -164,11 +164,11 @@ __device__ __forceinline__ void swap_units(
 template <bool OUT, bool NT_POOL_ST>
 __global__ __launch_bounds__(kPartThreads) void swap_runs_kernel(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const RunDesc* __restrict__ descs,
-    uint32_t ndesc, uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
-    uint64_t chunk_bytes, uint64_t pool_lstride) {
+    uint32_t ndesc, uint32_t row, uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts,
+    uint32_t total, uint64_t chunk_bytes, uint64_t pool_lstride) {
     swap_parts<OUT, NT_POOL_ST>(
-        pool, img, [&](uint32_t k) { return descs[k]; }, ndesc, l0, img_l0, units, parts, total,
-        chunk_bytes, pool_lstride);
+        pool, img, [&](uint32_t k) { return descs[k]; }, ndesc, row, l0, img_l0, units, parts,
+        total, chunk_bytes, pool_lstride);
 }
 
 template <bool OUT, bool NT_POOL_ST>
@@ -189,10 +189,10 @@ __global__ __launch_bounds__(kMaxThreads) void swap_runs_whole_kernel(
 template <bool OUT, bool NT_POOL_ST, uint32_t CAP>
 __global__ __launch_bounds__(kPartThreads) void swap_runs_inline_kernel(
     uint8_t* __restrict__ pool, uint8_t* __restrict__ img, const InlineArg<CAP> runs,
-    uint32_t ndesc, uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts, uint32_t total,
-    uint64_t chunk_bytes, uint64_t pool_lstride) {
+    uint32_t ndesc, uint32_t row, uint32_t l0, uint32_t img_l0, uint32_t units, uint32_t parts,
+    uint32_t total, uint64_t chunk_bytes, uint64_t pool_lstride) {
     swap_parts<OUT, NT_POOL_ST>(
-        pool, img, [&](uint32_t k) { return unpack_inline(runs.run[k]); }, ndesc, l0, img_l0,
+        pool, img, [&](uint32_t k) { return unpack_inline(runs.run[k]); }, ndesc, row, l0, img_l0,
         units, parts, total, chunk_bytes, pool_lstride);
 }
 
@@ -289,9 +289,11 @@ hipError_t launch_with_event(const void* fn, uint32_t grid, uint32_t threads, vo
 }
 
 template <bool OUT, bool NT_POOL_ST>
-hipError_t launch_swap_k(const SwapLaunch& a, uint32_t l0, uint32_t units, hipStream_t stream,
+hipError_t launch_swap_k(const SwapLaunch& a, uint32_t l0, uint32_t nl, hipStream_t stream,
                          hipEvent_t done) {
     const bool whole = a.max_workgroups != 0 || a.xcd_units;
+    const uint32_t row = whole ? a.ndesc : layer_units(a.ndesc);
+    const uint32_t units = nl * row;
     const PartGrid g = part_grid(units, a.min_run_bytes, a.mean_run_bytes, a.max_run_bytes);
     const uint32_t grid = whole ? launch_grid(units, a.max_workgroups) : g.grid;
     const uint32_t threads = whole ? kMaxThreads : kPartThreads;
@@ -300,7 +302,7 @@ hipError_t launch_swap_k(const SwapLaunch& a, uint32_t l0, uint32_t units, hipSt
     // of the longer one.
     const uint32_t xcd = a.xcd_units;
     const void* runs = a.inl ? (const void*)a.inl : (const void*)&a.descs;
-    const void* part_args[] = {&a.pool,   &a.img, runs,     &a.ndesc, &l0,
+    const void* part_args[] = {&a.pool, &a.img,   runs,     &a.ndesc, &row,           &l0,
                                &a.img_l0, &units, &g.parts, &g.total, &a.chunk_bytes,
                                &a.pool_lstride};
     const void* whole_args[] = {&a.pool,   &a.img, runs,           &a.ndesc,        &l0,
@@ -336,16 +338,15 @@ hipError_t launch_swap(const SwapLaunch& a, hipStream_t stream, uint64_t* launch
                        hipEvent_t done) {
     if (!a.ndesc || !a.num_layers) return done ? hipEventRecord(done, stream) : hipSuccess;
     // Whole layers per launch, fewer than 2^31 units each.
-    const uint32_t per = layers_per_launch(a.ndesc);
+    const uint32_t per = layers_per_launch(layer_units(a.ndesc));
     const uint32_t end = a.first_layer + a.num_layers;
     for (uint32_t l0 = a.first_layer; l0 < end; l0 += per) {
         const uint32_t nl = std::min<uint32_t>(per, end - l0);
-        const uint32_t units = nl * a.ndesc;
         const hipEvent_t last = l0 + nl == end ? done : nullptr;
-        const hipError_t e = a.out ? launch_swap_k<true, false>(a, l0, units, stream, last)
+        const hipError_t e = a.out ? launch_swap_k<true, false>(a, l0, nl, stream, last)
                              : a.nt_pool_store
-                                 ? launch_swap_k<false, true>(a, l0, units, stream, last)
-                                 : launch_swap_k<false, false>(a, l0, units, stream, last);
+                                 ? launch_swap_k<false, true>(a, l0, nl, stream, last)
+                                 : launch_swap_k<false, false>(a, l0, nl, stream, last);
         if (e != hipSuccess) return e;
         if (launches) ++*launches;
     }

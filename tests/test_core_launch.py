@@ -11,6 +11,18 @@ from tests import core_lib
 K = 1 << 10
 
 
+@pytest.mark.parametrize("ndesc", [1, 7, 63, 64, 224, 225, 255, 256, 257, 263, 264, 2047, 4091])
+def test_runs_keep_their_xcd_from_layer_to_layer(ndesc):
+    """Every run of every layer once; from 256 runs on, padded to a multiple of
+    eight, each run on one XCD over all layers."""
+    fn = core_lib.lib().aqua_core_layer_hits
+    fn.argtypes, fn.restype = [ctypes.c_uint32] * 2 + [ctypes.c_void_p], ctypes.c_int32
+    hits = np.zeros(5 * ndesc, dtype=np.uint8)
+    same = fn(5, ndesc, hits.ctypes.data)
+    assert (hits == 1).all()
+    assert same == (ndesc % 8 == 0 or ndesc >= 256)
+
+
 def _part_grid(units, mean, longest):
     fn = core_lib.lib().aqua_core_part_grid
     fn.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_void_p]
