@@ -39,16 +39,16 @@ HOST_LINK_PEAK_GBS = 63.0    # PCIe 5.0 x16, one direction, after encoding
 # or to how they are launched reports null until measured again.
 # Recorded with the profile summary of the same kernel under profiles/.
 MEASURED_TRAFFIC = {
-    ("llama70b_hbm", "13417f258857070b"): {
-        "gather (swap-out)": 21478084809, "scatter (swap-in)": 21476892772},
-    ("llama8b_hbm", "13417f258857070b"): {
-        "gather (swap-out)": 4296124199, "scatter (swap-in)": 4295530800},
-    ("llama70b_tp2_hbm", "13417f258857070b"): {
-        "gather (swap-out)": 10739621776, "scatter (swap-in)": 10739296865},
-    ("llama70b_tp4_hbm", "13417f258857070b"): {
-        "gather (swap-out)": 5369594663, "scatter (swap-in)": 5369299960},
-    ("llama8b_fp8_hbm", "13417f258857070b"): {
-        "gather (swap-out)": 2148315120, "scatter (swap-in)": 2149326387},
+    ("llama70b_hbm", "d24b03372800018f"): {
+        "gather (swap-out)": 21475424356, "scatter (swap-in)": 21475302416},
+    ("llama8b_hbm", "d24b03372800018f"): {
+        "gather (swap-out)": 4295551990, "scatter (swap-in)": 4295161554},
+    ("llama70b_tp2_hbm", "d24b03372800018f"): {
+        "gather (swap-out)": 10739663424, "scatter (swap-in)": 10737802395},
+    ("llama70b_tp4_hbm", "d24b03372800018f"): {
+        "gather (swap-out)": 5369068990, "scatter (swap-in)": 5368998292},
+    ("llama8b_fp8_hbm", "d24b03372800018f"): {
+        "gather (swap-out)": 2147884844, "scatter (swap-in)": 2147674162},
 }
 
 # Every source that decides what the swap kernels do and how they are
