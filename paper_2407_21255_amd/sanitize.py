@@ -21,8 +21,8 @@ from paper_2407_21255_amd.build import CORE_SOURCES, CSRC, INCLUDE, ROOT
 OUT_DIR = os.path.join(ROOT, "_build", "sanitize")
 FLAGS = ["-fsanitize=address,undefined", "-fno-sanitize-recover=all",
          "-fno-omit-frame-pointer", "-g", "-O1"]
-TESTS = ["tests/test_core_plan.py", "tests/test_core_hazards.py", "tests/test_core_ranges.py",
-         "tests/test_core_links.py", "tests/test_oracle_pins.py",
+TESTS = ["tests/test_core_plan.py", "tests/test_core_launch.py", "tests/test_core_hazards.py",
+         "tests/test_core_ranges.py", "tests/test_core_links.py", "tests/test_oracle_pins.py",
          "tests/test_oracle_ext_pins.py"]
 
 
